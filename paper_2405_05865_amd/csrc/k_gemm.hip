@@ -28,9 +28,16 @@ constexpr int WAVE = 64;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
-typedef double nd2 __attribute__((ext_vector_type(2)));
-typedef float nf4 __attribute__((ext_vector_type(4)));
-typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
+// 16-byte chunks at the alignment of one element: global memory takes a 16-byte load at any
+// element address, so an odd leading dimension or base keeps the vector loads. The loads go
+// through the caches: a lane's 128 bytes of a row are two loads of one line per lane group,
+// and with an odd leading dimension a line is shared by two steps, so loads marked as
+// streamed fetched lines twice. FP64, 16 columns, n = 10007 with lda = n: 651 us per sweep
+// with element loads, 418 us with streamed 16-byte loads, 274 us with these (8 segments
+// each); n = 32768: 1.64 ms streamed, 1.42 ms with these (6.0 TB/s).
+typedef double nd2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float nf4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t nu4 __attribute__((ext_vector_type(4), aligned(2)));
 
 template <class TC>
 struct V4;
@@ -65,7 +72,7 @@ template <>
 struct Ld<double, double> {
   static constexpr int VEC = 2;
   __device__ static void vec(const double* p, double* o) {
-    const nd2 v = __builtin_nontemporal_load(reinterpret_cast<const nd2*>(p));
+    const nd2 v = *reinterpret_cast<const nd2*>(p);
     o[0] = v.x;
     o[1] = v.y;
   }
@@ -75,7 +82,7 @@ template <>
 struct Ld<float, float> {
   static constexpr int VEC = 4;
   __device__ static void vec(const float* p, float* o) {
-    const nf4 v = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(p));
+    const nf4 v = *reinterpret_cast<const nf4*>(p);
     o[0] = v.x;
     o[1] = v.y;
     o[2] = v.z;
@@ -87,7 +94,7 @@ template <>
 struct Ld<float, double> {
   static constexpr int VEC = 4;
   __device__ static void vec(const float* p, double* o) {
-    const nf4 v = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(p));
+    const nf4 v = *reinterpret_cast<const nf4*>(p);
     o[0] = v.x;
     o[1] = v.y;
     o[2] = v.z;
@@ -99,7 +106,7 @@ template <>
 struct Ld<__hip_bfloat16, float> {
   static constexpr int VEC = 8;
   __device__ static void vec(const __hip_bfloat16* p, float* o) {
-    const nu4 v = __builtin_nontemporal_load(reinterpret_cast<const nu4*>(p));
+    const nu4 v = *reinterpret_cast<const nu4*>(p);
     o[0] = bf_lo(v.x);
     o[1] = bf_hi(v.x);
     o[2] = bf_lo(v.y);
@@ -112,24 +119,18 @@ struct Ld<__hip_bfloat16, float> {
   __device__ static float one(const __hip_bfloat16* p) { return __bfloat162float(*p); }
 };
 
-// VEC consecutive FP64 vector entries (16-byte aligned when the vector's rows are),
-// converted to the arithmetic type
-template <class TC, int VEC, bool ALN>
+// VEC consecutive FP64 vector entries, converted to the arithmetic type
+template <class TC, int VEC>
 __device__ __forceinline__ void ld_x(const double* p, TC* o) {
-  if constexpr (ALN) {
 #pragma unroll
-    for (int q = 0; q < VEC / 2; ++q) {
-      const nd2 v = *reinterpret_cast<const nd2*>(p + 2 * q);
-      o[2 * q] = (TC)v.x;
-      o[2 * q + 1] = (TC)v.y;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < VEC; ++q) o[q] = (TC)p[q];
+  for (int q = 0; q < VEC / 2; ++q) {
+    const nd2 v = *reinterpret_cast<const nd2*>(p + 2 * q);
+    o[2 * q] = (TC)v.x;
+    o[2 * q + 1] = (TC)v.y;
   }
 }
 
-template <class TA, class TC, int RT, int KT, bool ALN>
+template <class TA, class TC, int RT, int KT>
 __global__ void __launch_bounds__(256) k_gemm(const TA* __restrict__ A, int64_t lda, int rows, int cols,
                                              const double* __restrict__ X, int64_t ldx, double* __restrict__ Y,
                                              int64_t ldy, int k, double lam, int diag,
@@ -148,7 +149,6 @@ __global__ void __launch_bounds__(256) k_gemm(const TA* __restrict__ A, int64_t 
   const int lane = threadIdx.x & (WAVE - 1), i = lane & 15, g = lane >> 4;
   const int r0 = rs * 16 * RT;
   const int gbase = cs * KT;  // first 16-column group of this wavefront
-  // X is read in aligned pairs only when the vectors' rows are 16-byte aligned
   const TA* ap[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) ap[t] = A + (int64_t)min(r0 + 16 * t + i, rows - 1) * lda + E * g;
@@ -164,23 +164,21 @@ __global__ void __launch_bounds__(256) k_gemm(const TA* __restrict__ A, int64_t 
 #pragma unroll
     for (int q = 0; q < KT; ++q) acc[t][q] = typename V4<TC>::t{0, 0, 0, 0};
   int c0 = cbeg;
-  if constexpr (ALN) {
 #pragma unroll 2
-    for (; c0 + STEP <= cend; c0 += STEP) {
-      TC a[RT][E], b[KT][E];
+  for (; c0 + STEP <= cend; c0 += STEP) {
+    TC a[RT][E], b[KT][E];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int h = 0; h < NCH; ++h) L::vec(ap[t] + c0 + h * VEC, a[t] + h * VEC);
+#pragma unroll
+    for (int q = 0; q < KT; ++q) ld_x<TC, E>(bp[q] + c0, b[q]);
+#pragma unroll
+    for (int m = 0; m < E; ++m)
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int h = 0; h < NCH; ++h) L::vec(ap[t] + c0 + h * VEC, a[t] + h * VEC);
-#pragma unroll
-      for (int q = 0; q < KT; ++q) ld_x<TC, E, true>(bp[q] + c0, b[q]);
-#pragma unroll
-      for (int m = 0; m < E; ++m)
-#pragma unroll
-        for (int t = 0; t < RT; ++t)
-#pragma unroll
-          for (int q = 0; q < KT; ++q) acc[t][q] = mfma(a[t][m], b[q][m], acc[t][q]);
-    }
+        for (int q = 0; q < KT; ++q) acc[t][q] = mfma(a[t][m], b[q][m], acc[t][q]);
   }
   for (; c0 < cend; c0 += STEP) {
     TC a[RT][E], b[KT][E];
@@ -265,10 +263,12 @@ __global__ void __launch_bounds__(WAVE) k_gemm_sum(const double* __restrict__ pa
   }
 }
 
-// segments of the reduction range: double until the launch has about 8 wavefronts per CU
-// (measured at n = 32768, 16 RHS: 2048 wavefronts stream faster than 8192 once every step
-// reads whole cache lines), each segment keeps >= min_seg columns and the partials fit the
-// scratch. Products of cache-resident matrices (the s x s operators of the inner levels,
+// segments of the reduction range: double until the launch has about 8 wavefronts per CU,
+// each segment keeps >= min_seg columns and the partials fit the scratch. A level-1 sweep
+// (min_seg = kSegSweep) wants the wavefronts more than long segments. FP64, 16 columns, us
+// per sweep by segment count: n = 4001: 130 with 2, 41 with 8, 36 with 16; n = 6000: 134
+// with 4, 72 with 16; n = 10007: 274 with 8, 235 with 16; n = 32768: 1382 with 4, 1462 with
+// 8. Products of cache-resident matrices (the s x s operators of the inner levels,
 // min_seg = kSegSmall) stop at about 4 wavefronts per CU: at s = 1024 and 512 columns fewer,
 // longer segments write and re-read fewer partials (a Schatten-1 block run 6% faster than
 // with 2048 wavefronts; 512 and 256 were slower)
@@ -299,14 +299,8 @@ hipError_t gemm_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
   const int seg_cols = (int)(((cols + nseg - 1) / nseg + STEP - 1) / STEP * STEP);
   const int64_t waves = (int64_t)nrs * ncs * nseg;
   const unsigned blocks = (unsigned)((waves + 3) / 4);
-  const bool aln = ((uintptr_t)A % 16 == 0) && ((lda * (int64_t)sizeof(TA)) % 16 == 0) && ((uintptr_t)X % 16 == 0) &&
-                   (ldx % 2 == 0);
-  if (aln)
-    hipLaunchKernelGGL((k_gemm<TA, TC, RT, KT, true>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols,
-                       X, ldx, Y, ldy, k, lam, diag ? 1 : 0, skip, dot_part, nrs, ncs, nseg, seg_cols, scratch);
-  else
-    hipLaunchKernelGGL((k_gemm<TA, TC, RT, KT, false>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols,
-                       X, ldx, Y, ldy, k, lam, diag ? 1 : 0, skip, dot_part, nrs, ncs, nseg, seg_cols, scratch);
+  hipLaunchKernelGGL((k_gemm<TA, TC, RT, KT>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols, X, ldx, Y,
+                     ldy, k, lam, diag ? 1 : 0, skip, dot_part, nrs, ncs, nseg, seg_cols, scratch);
   if (nseg > 1 && !defer_sum)
     hipLaunchKernelGGL(k_gemm_sum, dim3((unsigned)nrs, (unsigned)k), dim3(WAVE), 0, st, scratch, nseg, (int)rows, k, X,
                        ldx, Y, ldy, lam, diag ? 1 : 0, skip, dot_part);
@@ -320,7 +314,7 @@ hipError_t gemm_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
 template <class TA, class TC>
 hipError_t gemm_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X, int64_t ldx,
                   double* Y, int64_t ldy, int k, double lam, bool diag, const int32_t* skip, double* dot_part,
-                  int* nblocks, double* scratch, size_t scratch_doubles, int min_seg = 1024, int force_nseg = 0,
+                  int* nblocks, double* scratch, size_t scratch_doubles, int min_seg = kSegSweep, int force_nseg = 0,
                   int* nseg_out = nullptr, bool defer_sum = false) {
   if (k <= 16)
     return gemm_t<TA, TC, 4, 1>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks, scratch,
@@ -343,7 +337,7 @@ int gemm_kt(int k, bool tc64) { return k <= 16 ? 1 : ((tc64 || k <= 32) ? 2 : 4)
 // rows and differ in the right-hand-side group, so A is reused from cache. Row ranges
 // are split when there are too few column tiles to fill the chip; the splits are summed
 // in fixed order afterwards.
-template <class TA, class TC, int KT, bool ALN>
+template <class TA, class TC, int KT>
 __global__ void __launch_bounds__(256) k_gemm_t(const TA* __restrict__ A, int64_t lda, int rows, int cols,
                                                const double* __restrict__ X, int64_t ldx, int k, int nct, int ncs,
                                                int nsplit, int rows_per_split, double* __restrict__ out, int64_t ldo,
@@ -357,7 +351,7 @@ __global__ void __launch_bounds__(256) k_gemm_t(const TA* __restrict__ A, int64_
   const int c0 = ct * 16 * VEC;
   const int cl = c0 + VEC * i;  // this lane's first A-column
   const int rb = sp * rows_per_split, re = min(rows, rb + rows_per_split);
-  const bool full = ALN && (cl + VEC <= cols);
+  const bool full = cl + VEC <= cols;
   const double* xp[KT];
 #pragma unroll
   for (int q = 0; q < KT; ++q) xp[q] = X + (int64_t)min(16 * (cs * KT + q) + i, k - 1) * ldx;
@@ -434,16 +428,11 @@ hipError_t gemmT_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int6
   gemmT_split(rows, cols, k, VEC, KT, &nsplit, &rps);
   const int64_t waves = (int64_t)nct * ncs * nsplit;
   const unsigned blocks = (unsigned)((waves + 3) / 4);
-  const bool aln = ((uintptr_t)A % 16 == 0) && ((lda * (int64_t)sizeof(TA)) % 16 == 0);
   const int direct = nsplit == 1;
   double* out = direct ? Y : part;
   const int64_t ldo = direct ? ldy : 0;
-  if (aln)
-    hipLaunchKernelGGL((k_gemm_t<TA, TC, KT, true>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols, X,
-                       ldx, k, nct, ncs, nsplit, rps, out, ldo, skip, direct);
-  else
-    hipLaunchKernelGGL((k_gemm_t<TA, TC, KT, false>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols, X,
-                       ldx, k, nct, ncs, nsplit, rps, out, ldo, skip, direct);
+  hipLaunchKernelGGL((k_gemm_t<TA, TC, KT>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols, X, ldx, k, nct,
+                     ncs, nsplit, rps, out, ldo, skip, direct);
   if (!direct) {
     const int64_t len = cols * k;
     hipLaunchKernelGGL(k_sum_splits_t, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, part, nsplit, cols, k,
@@ -496,16 +485,16 @@ hipError_t launch_gemm_split(hipStream_t st, const void* A, msp_dtype a_t, bool 
   switch (a_t) {
     case MSP_F64:
       return gemm_k<double, double>(st, (const double*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam, diag, skip,
-                                    dot_part, nblocks, scratch, scratch_doubles, 1024, nseg);
+                                    dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
     case MSP_F32:
       if (fp64_arith)
         return gemm_k<float, double>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam, diag, skip,
-                                     dot_part, nblocks, scratch, scratch_doubles, 1024, nseg);
+                                     dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
       return gemm_k<float, float>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam, diag, skip, dot_part,
-                                  nblocks, scratch, scratch_doubles, 1024, nseg);
+                                  nblocks, scratch, scratch_doubles, kSegSweep, nseg);
     case MSP_BF16:
       return gemm_k<__hip_bfloat16, float>(st, (const __hip_bfloat16*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam,
-                                           diag, skip, dot_part, nblocks, scratch, scratch_doubles, 1024, nseg);
+                                           diag, skip, dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
   }
   return hipErrorInvalidValue;
 }
@@ -516,7 +505,7 @@ int gemm_split_default(int64_t rows, int64_t cols, int64_t k, msp_dtype a_t, boo
   const int kt = gemm_kt((int)k, tc64);
   const int64_t nrs = (rows + 63) / 64;
   const int64_t ncs = (((k + 15) / 16) + kt - 1) / kt;
-  return gemm_segments(rows, cols, (int)k, nrs * ncs, scratch_doubles, 1024);
+  return gemm_segments(rows, cols, (int)k, nrs * ncs, scratch_doubles, kSegSweep);
 }
 
 hipError_t launch_gemm(hipStream_t st, const void* A, msp_dtype a_t, bool fp64_arith, int64_t rows, int64_t cols,

@@ -19,9 +19,11 @@ __device__ __forceinline__ T wsum(T v) {
   return v;
 }
 
-typedef double nd2 __attribute__((ext_vector_type(2)));
-typedef float nf4 __attribute__((ext_vector_type(4)));
-typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
+// 16-byte chunks at the alignment of one element: a global load takes them at any element
+// address, so an odd leading dimension or base keeps the vector loads
+typedef double nd2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float nf4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t nu4 __attribute__((ext_vector_type(4), aligned(2)));
 
 // VEC elements of A per 16-byte load, converted to TC
 template <class TA, class TC, int VEC>
@@ -74,19 +76,9 @@ __device__ __forceinline__ float scalar_as<__hip_bfloat16, float>(const __hip_bf
   return __bfloat162float(*p);
 }
 
-template <class TA, class TC, int VEC, bool ALN>
-__device__ __forceinline__ void load_vec(const TA* p, TC* o) {
-  if constexpr (ALN) {
-    Vec16<TA, TC, VEC>::load(p, o);
-  } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) o[v] = scalar_as<TA, TC>(p + v);
-  }
-}
-
 // Block of NT threads computes R rows of Y = A X (+ lam X) for K vectors; each thread
 // keeps UNR 16-byte loads per row in flight.
-template <class TA, class TC, int VEC, int R, int K, bool ALN, int UNR>
+template <class TA, class TC, int VEC, int R, int K, int UNR>
 __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t lda, int64_t rows, int64_t cols,
                                             const double* __restrict__ X, int64_t ldx, double* __restrict__ Y,
                                             int64_t ldy, int k, int j0, double lam, int diag,
@@ -113,7 +105,7 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
 #pragma unroll
-      for (int r = 0; r < R; ++r) load_vec<TA, TC, VEC, ALN>(arow[r] + c + u * STEP, a[u][r]);
+      for (int r = 0; r < R; ++r) Vec16<TA, TC, VEC>::load(arow[r] + c + u * STEP, a[u][r]);
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       TC xv[K][VEC];
@@ -142,7 +134,7 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       TC a[VEC];
-      load_vec<TA, TC, VEC, ALN>(arow[r] + c, a);
+      Vec16<TA, TC, VEC>::load(arow[r] + c, a);
 #pragma unroll
       for (int j = 0; j < K; ++j)
 #pragma unroll
@@ -194,7 +186,7 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
 }
 
 // Y[:, j] = A^T X[:, j]: block (column tile, row tile); partial over the row tile
-template <class TA, class TC, int VEC, int K, bool ALN>
+template <class TA, class TC, int VEC, int K>
 __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t lda, int64_t rows, int64_t cols,
                                               const double* __restrict__ X, int64_t ldx, int k, int j0,
                                               int64_t rows_per_tile, double* __restrict__ part) {
@@ -210,7 +202,7 @@ __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t
   for (int64_t r = rb; r < re; ++r) {
     TC a[VEC];
     if (full) {
-      load_vec<TA, TC, VEC, ALN>(A + r * lda + c, a);
+      Vec16<TA, TC, VEC>::load(A + r * lda + c, a);
     } else {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) a[v] = (c + v < cols) ? scalar_as<TA, TC>(A + r * lda + c + v) : (TC)0;
@@ -245,25 +237,14 @@ __global__ void k_sum_tiles(const double* __restrict__ part, int tiles, int64_t 
   Y[(int64_t)j * ldy + c] = acc;
 }
 
-template <class TA>
-bool aligned16(const TA* A, int64_t lda) {
-  return ((uintptr_t)A % 16 == 0) && ((lda * (int64_t)sizeof(TA)) % 16 == 0);
-}
-
 template <class TA, class TC, int VEC, int R, int K, int UNR = 1>
 hipError_t gemv_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X,
                   int64_t ldx, double* Y, int64_t ldy, int k, double lam, bool diag, const int32_t* skip,
                   double* dot_part, int* nblocks) {
   const int64_t blocks = (rows + R - 1) / R;
-  const bool aln = aligned16(A, lda);
-  for (int j0 = 0; j0 < k; j0 += K) {
-    if (aln)
-      hipLaunchKernelGGL((k_gemv<TA, TC, VEC, R, K, true, UNR>), dim3((unsigned)blocks), dim3(NT), 0, st, A, lda, rows,
-                         cols, X, ldx, Y, ldy, k, j0, lam, diag ? 1 : 0, skip, dot_part, k);
-    else
-      hipLaunchKernelGGL((k_gemv<TA, TC, VEC, R, K, false, UNR>), dim3((unsigned)blocks), dim3(NT), 0, st, A, lda, rows,
-                         cols, X, ldx, Y, ldy, k, j0, lam, diag ? 1 : 0, skip, dot_part, k);
-  }
+  for (int j0 = 0; j0 < k; j0 += K)
+    hipLaunchKernelGGL((k_gemv<TA, TC, VEC, R, K, UNR>), dim3((unsigned)blocks), dim3(NT), 0, st, A, lda, rows, cols, X,
+                       ldx, Y, ldy, k, j0, lam, diag ? 1 : 0, skip, dot_part, k);
   if (nblocks) *nblocks = (int)blocks;
   return hipGetLastError();
 }
@@ -288,15 +269,9 @@ hipError_t gemvT_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int6
   if (rtiles > rows) rtiles = rows;
   const int64_t rpt = (rows + rtiles - 1) / rtiles;
   rtiles = (rows + rpt - 1) / rpt;
-  const bool aln = aligned16(A, lda);
-  for (int j0 = 0; j0 < k; j0 += K) {
-    if (aln)
-      hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, K, true>), dim3((unsigned)ctiles, (unsigned)rtiles), dim3(NT), 0, st,
-                         A, lda, rows, cols, X, ldx, k, j0, rpt, part);
-    else
-      hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, K, false>), dim3((unsigned)ctiles, (unsigned)rtiles), dim3(NT), 0, st,
-                         A, lda, rows, cols, X, ldx, k, j0, rpt, part);
-  }
+  for (int j0 = 0; j0 < k; j0 += K)
+    hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, K>), dim3((unsigned)ctiles, (unsigned)rtiles), dim3(NT), 0, st, A, lda,
+                       rows, cols, X, ldx, k, j0, rpt, part);
   const int64_t len = cols * k;
   hipLaunchKernelGGL(k_sum_tiles, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, part, (int)rtiles, cols, k,
                      skip, Y, ldy);

@@ -161,8 +161,8 @@ int sketch_rows_choice(msp_dtype a_t, int64_t m, int64_t n, int64_t lda, int64_t
 // Y[:, j] = M X[:, j] for an FP64 row-major M (ld = cols) with few rows: the same
 // matrix-core product, its reduction range cut into segments of at least min_seg columns
 // until about 2048 wavefronts run (scratch of at least gemm_split_doubles(rows, k)
-// doubles). The level-1 sweep keeps min_seg = 1024 (long streams from HBM); the s x s
-// inner operators, which stay in cache, take 64; the s x n level-2 factor takes 256.
+// doubles). The level-1 sweep keeps segments of kSegSweep columns or more; the s x s inner
+// operators, which stay in cache, take 64; the s x n level-2 factor takes 256.
 // With defer_sum and more than one segment the segment partials stay in the scratch
 // (layout [segment][column][row], *nseg_out segments) for the consumer to add in order.
 hipError_t launch_gemm_seg(hipStream_t st, const double* M, int64_t rows, int64_t cols, const double* X,
@@ -170,6 +170,7 @@ hipError_t launch_gemm_seg(hipStream_t st, const double* M, int64_t rows, int64_
                            size_t scratch_doubles, int min_seg, int* nseg_out = nullptr, bool defer_sum = false);
 constexpr int kSegSmall = 64;
 constexpr int kSegWide = 256;
+constexpr int kSegSweep = 192;
 // Y[:, j] = A^T X[:, j] on the matrix cores for k >= kGemmMinK (same contract as
 // launch_gemv_t; part: gemv_t_part_doubles(rows, cols, k) doubles)
 size_t gemm_t_part_doubles(int64_t rows, int64_t cols, int64_t k);  // its split partials
