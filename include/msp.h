@@ -21,7 +21,11 @@
  *     Arguments are validated before any device work is enqueued. msp_last_error()
  *     returns a thread-local message describing the last failure.
  *   - Determinism: identical inputs, seeds and device give bitwise-identical results
- *     (all reductions run in a fixed order; no floating-point atomics).
+ *     (all reductions run in a fixed order; no floating-point atomics). The one exception:
+ *     an inner solve runs as one launch whose blocks wait for each other; when other work
+ *     keeps them from running together for 50 ms (MSP_INNER_WAIT_MS in the environment sets
+ *     another time), the solve is run again with one or two launches per inner step, whose
+ *     sums differ by rounding.
  */
 #ifndef MSP_H
 #define MSP_H
@@ -236,7 +240,8 @@ typedef struct {
                               formed operator (the PSD level 2, the general level 3) as one HIP
                               graph, captured once per solve, operator and chunk length and
                               replayed on the solve's stream. Same kernels and results as the
-                              eager launches. Default 0. */
+                              eager launches. Inner solves that run as one launch (s <= 1024)
+                              have no steps to replay. Default 0. */
   int32_t batch_teams;     /* msp_solve_batched: a workgroup whose system is finished helps the
                               A-sweeps of a larger unfinished system (same results bit for bit;
                               chunked partials in a fixed order). Default 1. */
@@ -249,8 +254,9 @@ typedef struct {
                               while timing; results differ from the built-in choice only by
                               summation order. Default 0 (built-in rule: about 2048
                               wavefronts). */
-  int32_t level3_kernels;  /* general, level2_form 1, k <= 16: kernels per level-3 step. 2 (default):
-                              the step as two kernels (decision, direction and operator product;
+  int32_t level3_kernels;  /* general, level2_form 1: how the level-3 steps run. 2 (default): both
+                              level-3 solves of a SolveM2 as one launch for s <= 1024 (few
+                              enough columns); else, for k <= 16, the step as two kernels (decision, direction and operator product;
                               step length, residual, preconditioner product and dots), every
                               product a direct FP64 row dot over the formed s x s matrices;
                               0: the generic inner step (an operator product, a residual update,

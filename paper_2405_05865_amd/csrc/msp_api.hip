@@ -73,7 +73,11 @@ constexpr int64_t kMaxS = 2048;    // tall-kernel register layout bound (32 colu
 constexpr int64_t kMaxK = 1024;
 
 // host mirror slots (pinned, mapped): [level*4 + 0] active count
-enum { SLOT_L1 = 0, SLOT_L2 = 4, SLOT_L3 = 8, SLOT_L3B = 12, SLOT_L0 = 16 };
+enum { SLOT_L1 = 0, SLOT_L2 = 4, SLOT_L3 = 8, SLOT_L3B = 12, SLOT_L0 = 16, SLOT_FAIL = 20 };
+
+// internal status: a one-launch inner solve gave up waiting for its blocks; the solve runs
+// again on the per-step kernels (never returned to the caller)
+constexpr msp_status kPcgGaveUp = (msp_status)15;
 
 // ------------------------------------------------------------------------------------
 // Sketch workspace layout
@@ -524,6 +528,10 @@ struct SolveCtx {
   // general level 3 under level2_form 1 with k <= kL2fMaxK: two kernels per step
   bool use_f = false;
   L2fArgs F{};
+  // inner solves on formed operators in one launch (k_pcg.hip); use_x / use_f (k <= 16) or the
+  // generic step then only run when such a solve gives up
+  bool use_p = false;
+  PcgRun pcg{};
   int32_t* hf;
   int32_t* df;
   int last_inner = 4, last_l3a = 4, last_l3b = 4;
@@ -533,6 +541,15 @@ struct SolveCtx {
   std::vector<hipEvent_t>* evpool = nullptr;
   size_t evused = 0;
 };
+
+// the one-launch inner solve against the per-step kernels: a launch's steps cost 1.3 to 12 us
+// however many groups it holds (k_pcg.hip), the per-step kernels 6 to 12 us (PSD) or 10 to 36
+// us (general) for up to 16 columns and about 42 us beyond, so a solve may take some launches
+// one after the other
+bool pcg_wins(int64_t s, int64_t k) {
+  const PcgShape h = pcg_shape(s, k);
+  return h.cpl > 0 && h.launches <= (k <= kL2xMaxK ? 4 : 8);
+}
 
 size_t solve_layout(WsCarver& w, const msp_precond* P, int64_t k, SolveCtx* c, int form, int sym, int l3k) {
   const int64_t n = P->n, m = P->m, s = P->s;
@@ -588,13 +605,17 @@ size_t solve_layout(WsCarver& w, const msp_precond* P, int64_t k, SolveCtx* c, i
   // ill-conditioned as the general level-3 matrices (A~^T A~ with kappa(A)^2 spread): there
   // the recurrence iterate stalls near 1e-4 relative error where direct products reach
   // 1e-7, and the outer levels take about three times the oracle's steps
-  const bool use_x = form == 1 && P->structure == MSP_SYM_PSD && s >= kGemmMinK && s <= kL2xMaxS && k <= kL2xMaxK;
+  const bool psd = P->structure == MSP_SYM_PSD;
+  const bool use_x = form == 1 && psd && s >= kGemmMinK && s <= kL2xMaxS && k <= kL2xMaxK;
+  // whole inner solves in one launch: the PSD level 2 by the same recurrence, the general
+  // level 3 by direct products
+  const bool use_p = form == 1 && s >= kGemmMinK && (psd || l3k == 2) && pcg_wins(s, k);
+  PcgRun pcg{};
+  if (use_p) pcg = pcg_carve(w, s, k);
   L2xArgs X{};
   double* G2 = nullptr;
-  if (use_x) {
-    X = l2x_carve(w, s, k);
-    G2 = w.take<double>(s * s);
-  }
+  if (use_x) X = l2x_carve(w, s, k);
+  if (use_x || (use_p && psd)) G2 = w.take<double>(s * s);
   // the general level 3 as two kernels per step (level2_form 1, at most kL2fMaxK columns)
   const bool use_f = form == 1 && P->structure == MSP_GENERAL && l3k == 2 && k <= kL2fMaxK && s <= kL2fMaxS;
   L2fArgs F{};
@@ -611,6 +632,8 @@ size_t solve_layout(WsCarver& w, const msp_precond* P, int64_t k, SolveCtx* c, i
     c->gemmpart_n = gemmpart_n;
     c->use_x = use_x;
     c->X = X;
+    c->use_p = use_p;
+    c->pcg = pcg;
     c->use_f = use_f;
     c->F = F;
     c->G2 = G2;
@@ -653,7 +676,7 @@ inline volatile int32_t* slot(SolveCtx& c, int i) { return (volatile int32_t*)(c
 
 msp_status sync(SolveCtx& c) {
   MSP_CHECK_HIP(hipStreamSynchronize(c.st));
-  return MSP_OK;
+  return *slot(c, SLOT_FAIL) ? kPcgGaveUp : MSP_OK;
 }
 
 // profiled sweeps: an event pair around each level-1 sweep launch
@@ -1041,7 +1064,7 @@ msp_status build_explicit(SolveCtx& c) {
     else
       MSP_CHECK_HIP(launch_gram_f32(c.st, (const float*)P->Y, n, s, P->ldy, c.H2, c.gtmp, sp));
     MSP_CHECK_HIP(launch_combine_sym(c.st, s, 1.0, c.H2, P->lt, P->Wm, 0.0, c.H2));
-    if (c.use_x) TRY(form_g(c, c.H2, P->Minv, c.G2));
+    if (c.use_x || c.use_p) TRY(form_g(c, c.H2, P->Minv, c.G2));
     return invert_h2(c);
   }
   int nb = 0;
@@ -1080,6 +1103,23 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
     MSP_CHECK_HIP(
         launch_y_z(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, k, 1.0 / P->lt, r, n, -1.0 / P->lt, pdone, z, n));
     TRY(sync(c));  // the level-1 mirror is read by the caller after SolveM1
+    return MSP_OK;
+  }
+  if (c.use_p) {  // the whole solve in one launch, H applied through G2 = H M2^{-1}
+    MSP_CHECK_HIP(l2_reduce_to(c.st, a, c.rhs2, pdone));
+    PcgArgs p{};
+    p.H = c.G2;
+    p.Minv[0] = P->Minv;
+    p.nsol = 1;
+    p.rhs = c.rhs2;
+    p.out = c.L2.x;
+    p.parent_done = pdone;
+    p.tol = c.o->inner_tol;
+    p.max_iter = c.o->max_inner;
+    p.fail_mirror = c.df + SLOT_FAIL;
+    MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, 0));
+    MSP_CHECK_HIP(
+        launch_y_z(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, k, 1.0 / P->lt, r, n, -1.0 / P->lt, pdone, z, n));
     return MSP_OK;
   }
   if (c.use_x) {  // one kernel per step on H = C^T C + lam~ W through G2 = H M2^{-1}
@@ -1122,7 +1162,8 @@ msp_status psd_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
   MSP_CHECK_HIP(fcg_first_dir(c.st, L.S, n, L.r, L.z, L.p));
   int it = 0;
   while (true) {
-    // the level-1 mirror is current: psd_solve_m1 synchronised after the update
+    // the level-1 mirror is current where psd_solve_m1 synchronised after the update
+    if (c.use_p) TRY(sync(c));
     if (*slot(c, SLOT_L1) == 0) {
       TRY(sweep(c, c.A_cf, c.cf_t, n, n, L.x, n, L.q, n, true, nullptr, false, true, false));
       MSP_CHECK_HIP(launch_axpby(c.st, n, k, 1.0, B, ldb, -1.0, L.q, n, L.q, n, nullptr));
@@ -1183,6 +1224,23 @@ msp_status gen_level3(SolveCtx& c, const double* rhs, double* out, double sigma,
 // SolveM2 (Algorithm 5) in the product form z = W^{-1} ((W + lam~ I)^{-1} r)
 msp_status gen_solve_m2(SolveCtx& c, const double* r, double* z, const int32_t* parent_done) {
   const msp_precond* P = c.P;
+  if (c.use_p) {  // both level-3 solves in one launch
+    PcgArgs p{};
+    p.H = c.H3;
+    p.Minv[0] = P->Minv2;
+    p.sigma[0] = P->lt;
+    p.Minv[1] = P->Minv;
+    p.sigma[1] = 0.0;
+    p.nsol = 2;
+    p.rhs = r;
+    p.out = z;
+    p.parent_done = parent_done;
+    p.tol = c.o->level3_tol;
+    p.max_iter = c.o->max_level3;
+    p.fail_mirror = c.df + SLOT_FAIL;
+    MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, 1));
+    return MSP_OK;
+  }
   TRY(gen_level3(c, r, c.tmp_s, P->lt, P->Minv2, parent_done, &c.last_l3b));
   TRY(gen_level3(c, c.tmp_s, z, 0.0, P->Minv, parent_done, &c.last_l3a));
   return MSP_OK;
@@ -1526,7 +1584,7 @@ msp_status choose_segments(SolveCtx& c) {
 }
 
 // the whole solve into X; status from the residuals
-msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B, int64_t ldb, double* X,
+msp_status solve_pass(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B, int64_t ldb, double* X,
                       int64_t ldx, msp_solve_info* info) {
   const msp_solve_opts* o = c.o;
   msp_status st = MSP_OK;
@@ -1564,7 +1622,12 @@ msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const doubl
   TRY(ev_collect(c));
   std::vector<int32_t> done(c.k);
   MSP_CHECK_HIP(hipMemcpyAsync(done.data(), c.L1.S.done, sizeof(int32_t) * c.k, hipMemcpyDeviceToHost, c.st));
+  PcgCtl ctl{};
+  if (c.use_p) MSP_CHECK_HIP(hipMemcpyAsync(&ctl, c.pcg.ctl, sizeof ctl, hipMemcpyDeviceToHost, c.st));
   MSP_CHECK_HIP(hipStreamSynchronize(c.st));
+  if (ctl.fail) return kPcgGaveUp;
+  (c.P->structure == MSP_SYM_PSD ? c.acc.inner_iters : c.acc.level3_iters) +=
+      ctl.total + ctl.it[0][0] + ctl.it[0][1] + ctl.it[1][0] + ctl.it[1][1];
   double worst = 0.0;
   for (int64_t j = 0; j < c.k; ++j) {
     worst = std::max(worst, rel[j]);
@@ -1583,6 +1646,24 @@ msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const doubl
   if (st == MSP_ERR_BREAKDOWN) msp_fail(st, "breakdown: p^T A p <= 0");
   if (st == MSP_ERR_NONFINITE) msp_fail(st, "non-finite residual");
   return st;
+}
+
+msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B, int64_t ldb, double* X,
+                      int64_t ldx, msp_solve_info* info) {
+  const msp_status st = solve_pass(c, A_hi, hi_t, B, ldb, X, ldx, info);
+  if (st != kPcgGaveUp) return st;
+  // some other work kept the blocks of an inner solve from running together: the same solve
+  // from the start with one or two launches per inner step
+  if (log_on()) fprintf(stderr, "[msp] an inner solve gave up waiting for its blocks: per-step kernels\n");
+  MSP_CHECK_HIP(hipStreamSynchronize(c.st));
+  c.use_p = false;
+  *slot(c, SLOT_FAIL) = 0;
+  c.acc = msp_solve_info{};
+  c.A_cf = A_hi;
+  c.cf_t = hi_t;
+  c.lam_sw = c.lam;
+  c.evused = 0;
+  return solve_pass(c, A_hi, hi_t, B, ldb, X, ldx, info);
 }
 
 msp_status make_ctx(SolveCtx& c, void* stream, const msp_precond* P, const void* A_hi, msp_dtype hi_t,
@@ -1610,7 +1691,14 @@ msp_status make_ctx(SolveCtx& c, void* stream, const msp_precond* P, const void*
   solve_layout(w, P, k, &c, o->level2_form, o->sym_sweep, o->level3_kernels);
   if (!w.ok()) return msp_fail(MSP_ERR_WORKSPACE, "workspace overflow");
   // the explicit general operators need the block transposed product (s >= 8)
-  if (P->structure == MSP_GENERAL && P->s < kGemmMinK) c.form = 0;
+  if (P->structure == MSP_GENERAL && P->s < kGemmMinK) {
+    c.form = 0;
+    c.use_f = false;
+  }
+  const int inner_cap = P->structure == MSP_SYM_PSD ? o->max_inner : o->max_level3;
+  if (inner_cap > kPcgMaxIter) c.use_p = false;
+  *slot(c, SLOT_FAIL) = 0;
+  if (c.use_p) MSP_CHECK_HIP(pcg_reset(c.st, c.pcg));
   for (Level* L : {&c.L0, &c.L1, &c.L2, &c.L3}) MSP_CHECK_HIP(hipMemsetAsync(L->S.counter, 0, sizeof(int32_t), c.st));
   MSP_CHECK_HIP(hipMemsetAsync(c.l2b, 0, sizeof(double) * l2_bpart_doubles(c.s, k), c.st));
   return MSP_OK;

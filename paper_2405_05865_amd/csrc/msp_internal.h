@@ -418,6 +418,64 @@ hipError_t l2f_op(hipStream_t st, const L2fArgs& a, int t, int fresh);
 hipError_t l2f_prec(hipStream_t st, const L2fArgs& a, int t);
 
 // ---------------------------------------------------------------------------------
+// Whole inner solves in one launch (k_pcg.hip) for s <= kPcgMaxS: operands in registers,
+// product rows exchanged between the blocks of a group through tagged words.
+// ---------------------------------------------------------------------------------
+constexpr int kPcgMaxS = 1024;
+constexpr int kPcgMaxBlocks = 64;      // blocks of a launch (they wait for each other)
+constexpr int kPcgMaxIter = 1 << 24;   // exchanges of a launch are numbered in 32 bits
+constexpr int64_t kPcgWait = 5000000;  // 50 ms of the 100 MHz wall clock
+struct PcgShape {
+  int cpl;       // 64-column chunks (1, 2, 4, 8, 16); 0: not supported
+  int nblk;      // blocks per group
+  int kc;        // columns per group
+  int groups;    // groups of the k columns
+  int per;       // groups per launch
+  int launches;  // launches per solve
+};
+struct PcgCtl {
+  int64_t total;   // iterations of the finished solves (largest over the columns, summed)
+  int32_t it[2][2];  // [solve parity][chained solve] of the solves not yet in total
+  int32_t fail;    // a wait ran out: the results are not valid
+};
+struct PcgRun {  // host side: the buffers and the exchange numbers of one msp_solve
+  PcgShape shape;
+  int s, k;
+  uint64_t* ex;
+  size_t words;
+  PcgCtl* ctl;
+  uint64_t next;
+  int parity;
+  int64_t wait;
+};
+struct PcgArgs {
+  // set by the caller
+  const double* H;        // operator (mode 1) or G = H Minv (mode 0), s x s row-major
+  const double* Minv[2];  // preconditioner of each chained solve
+  double sigma[2];        // mode 1: operator H + sigma I
+  int nsol;               // chained solves (mode 1: 1 or 2; mode 0: 1)
+  const double* rhs;      // [k][s]
+  double* out;            // [k][s]; zero for columns finished one level up
+  const int32_t* parent_done;
+  double tol;
+  int max_iter;
+  int32_t* fail_mirror;  // host-mapped copy of ctl->fail
+  // set by pcg_solve
+  int s, k, nblk, col0, parity;
+  uint64_t* ex;
+  int64_t ex_stride;
+  PcgCtl* ctl;
+  int64_t wait;
+  uint32_t ep0;
+};
+PcgShape pcg_shape(int64_t s, int64_t k);
+PcgRun pcg_carve(WsCarver& w, int64_t s, int64_t k);
+hipError_t pcg_reset(hipStream_t st, PcgRun& R);  // once per msp_solve
+// mode 0: one solve with G and Minv by the recurrence of k_l2x.hip; mode 1: nsol chained
+// solves by direct products (the solution of one is the right-hand side of the next)
+hipError_t pcg_solve(hipStream_t st, PcgRun& R, PcgArgs a, int mode);
+
+// ---------------------------------------------------------------------------------
 // The preconditioner handle
 // ---------------------------------------------------------------------------------
 struct msp_precond {
