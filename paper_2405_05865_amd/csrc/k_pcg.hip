@@ -31,9 +31,10 @@
 // whole solve on the per-step kernels. So every wait ends.
 //
 // Measured per step, launch and operand loads included: s = 32, direct form, one block: 1.3 us
-// (two kernels per step: 9.9 us); s = 384, recurrence, one column: 3.5 us (6.0 us); s = 256,
-// 64 columns, direct form, two launches of 32 columns each: 13.4 us for all of them (the
-// generic step: 42 us); s = 512, 8 columns, direct: 9.9 us (14.5 us).
+// (two kernels per step: 9.9 us); s = 384, recurrence, one column: 3.3 us (6.0 us); s = 512,
+// 8 columns, direct, two columns per group: 5.6 us (four per group: 9.8 us; two kernels per
+// step: 14.5 us); s = 256, 64 columns, direct, eight columns per group in one launch: 8.3 us
+// (four per group in two launches: 13.4 us; the generic step: 42 us).
 #include <cstdlib>
 
 #include "msp_internal.h"
@@ -62,7 +63,7 @@ struct Block {
   static constexpr int SP = CPL * WAVE;              // padded length
   static constexpr int NV = KC * SP;                 // elements of a vector block
   static constexpr int EPT = (NV + NT - 1) / NT;     // per thread: e = tid + q NT
-  static constexpr int RC = KC == 1 ? (RPW < 8 ? RPW : 8) : (RPW < 2 ? RPW : 2);  // rows per reduction
+  static constexpr int RC = RPW * KC <= 16 ? RPW : (KC <= 2 ? 8 : 2);  // rows per reduction
 
   // LDS: xs the staged vector (zero beyond s), zr the product rows (one block), red the dot
   // partials by 64-element chunk, bc per-column scalars
@@ -265,12 +266,16 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
       if (e < NV) sh.xs[e] = x[q];
     }
   };
-  // active columns after the owners' decision dj (dj, when several columns, also to LDS)
-  auto publish_done = [&](int dj) -> bool {
+  // several columns: the owners' scalar v of `slot` and their decision dj go through LDS
+  // (one barrier); returns whether any column is active
+  auto publish = [&](int slot, double v, int dj) -> bool {
     if constexpr (KC == 1) {
       return dj == 0;
     } else {
-      if (tid < KC) sh.done[tid] = dj;
+      if (tid < KC) {
+        sh.done[tid] = dj;
+        sh.bc[slot][tid] = v;
+      }
       const uint64_t act = __ballot(tid < KC && dj == 0);
       if (tid == 0) sh.any = act != 0;
       __syncthreads();
@@ -278,12 +283,6 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
     }
   };
   auto col_done = [&](int q, int dj) -> bool { return KC == 1 ? dj != 0 : sh.done[ecol[q]] != 0; };
-  auto bcast = [&](int slot, double v) {
-    if constexpr (KC > 1) {
-      if (tid < KC) sh.bc[slot][tid] = v;
-      __syncthreads();
-    }
-  };
   auto scalar = [&](int slot, int q, double v) -> double { return KC == 1 ? v : sh.bc[slot][ecol[q]]; };
 
   bool failed = false;
@@ -305,13 +304,31 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
     int it = 0;
     const bool pd = k0 + oc >= a.k || (a.parent_done && a.parent_done[k0 + oc] != 0);
     int dj = (pd || bn == 0.0) ? 1 : 0;
-    bool any = publish_done(dj);
+    bool any = publish(0, 0.0, dj);
+    // the decision on the residual whose partials are in slot 2. With several blocks it is
+    // taken after the next product's rows are sent, in the shadow of their way: a product is
+    // lost at the end of a solve, a square root and a barrier are won in every step
+    bool brk = false;
+    auto decide = [&]() {
+      if (owner && dj == 0) {
+        const double rn = sqrt(B::total(2, 0, oc, sh));
+        ++it;
+        if (brk || !(rn == rn)) dj = 2;
+        else if (rn <= a.tol * bn) dj = 1;
+        else if (it >= a.max_iter) dj = 3;
+      }
+      return publish(1, 0.0, dj);
+    };
     if constexpr (MODE == 0) {
       bool first = true;
       while (any) {
         uint64_t* ex = exg + (ep & 1) * exn;
         B::product(mm, 0, s, row0, sh, ex, ep);
         B::product(hm, 1, s, row0, sh, ex, ep);
+        if (MULTI && !first && !decide()) {
+          ep += 2;  // nobody receives the rows just sent: the next exchange takes their buffer
+          break;    // (a slow block may still read the other one)
+        }
         if (!B::template receive<2>(s, k0, a.k, sh, ex, ep, a.wait, v2)) sh.stop = 1;
         ++ep;
         double zg[2][EPT];
@@ -338,7 +355,7 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
           rzbad = !first && !(rz != 0.0 && isfinite(rz));
           beta = (first || rzbad) ? 0.0 : -al * zu / rz;
         }
-        bcast(0, beta);
+        publish(0, beta, dj);
 #pragma unroll
         for (int q = 0; q < EPT; ++q) {
           const double bq = scalar(0, q, beta);
@@ -350,14 +367,15 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         }
         B::template partials<1>(v1, 1, sh);
         __syncthreads();
-        bool brk = false;
         double alpha = 0.0;
         if (owner && dj == 0) {
           const double pq = B::total(1, 0, oc, sh);
           brk = rzbad || !(pq > 0.0);
           alpha = brk ? 0.0 : zr / pq;
+          rz = zr;
+          al = alpha;
         }
-        bcast(1, alpha);
+        publish(1, alpha, dj);
 #pragma unroll
         for (int q = 0; q < EPT; ++q) {
           if (!col_done(q, dj)) {
@@ -370,17 +388,8 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         stage(r);
         B::template partials<1>(v1, 2, sh);
         __syncthreads();
-        if (owner && dj == 0) {
-          const double rn = sqrt(B::total(2, 0, oc, sh));
-          ++it;
-          if (brk || !(rn == rn)) dj = 2;
-          else if (rn <= a.tol * bn) dj = 1;
-          else if (it >= a.max_iter) dj = 3;
-          rz = zr;
-          al = alpha;
-        }
         first = false;
-        any = publish_done(dj);
+        if (!MULTI) any = decide();
       }
     } else {
       bool first = true;
@@ -389,6 +398,10 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         {
           uint64_t* ex = exg + (ep & 1) * exn;
           B::product(mm, 0, s, row0, sh, ex, ep);
+          if (MULTI && !first && !decide()) {
+            ep += 2;
+            break;
+          }
           if (!B::template receive<1>(s, k0, a.k, sh, ex, ep, a.wait, v1)) sh.stop = 1;
           ++ep;
         }
@@ -419,8 +432,7 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
             dj = 2;
           }
         }
-        bcast(0, beta);
-        if (!publish_done(dj)) break;
+        if (!publish(0, beta, dj)) break;
 #pragma unroll
         for (int q = 0; q < EPT; ++q)
           if (!col_done(q, dj)) p[q] = first ? z[q] : fma(scalar(0, q, beta), p[q], z[q]);
@@ -446,14 +458,13 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
           failed = true;
           break;
         }
-        bool brk = false;
         double alpha = 0.0;
         if (owner && dj == 0) {
           const double pq = B::total(1, 0, oc, sh);
           brk = !(pq > 0.0);
           alpha = brk ? 0.0 : rz / pq;
         }
-        bcast(1, alpha);
+        publish(1, alpha, dj);
 #pragma unroll
         for (int q = 0; q < EPT; ++q) {
           u[q] = r[q];
@@ -467,14 +478,7 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         stage(r);
         B::template partials<1>(v1, 2, sh);
         __syncthreads();
-        if (owner && dj == 0) {
-          const double rn = sqrt(B::total(2, 0, oc, sh));
-          ++it;
-          if (brk || !(rn == rn)) dj = 2;
-          else if (rn <= a.tol * bn) dj = 1;
-          else if (it >= a.max_iter) dj = 3;
-        }
-        any = publish_done(dj);
+        if (!MULTI) any = decide();
       }
     }
     // the most iterations of any column of the launch
@@ -507,8 +511,11 @@ hipError_t dispatch(hipStream_t st, const PcgArgs& a, const PcgShape& h, int gro
     case 101: return go<MODE, 1, 8, 1, false>(st, a, groups);
     case 201: return go<MODE, 2, 16, 1, false>(st, a, groups);
     case 401: return go<MODE, 4, 4, 1, true>(st, a, groups);
+    case 402: return go<MODE, 4, 4, 2, true>(st, a, groups);
     case 404: return go<MODE, 4, 4, 4, true>(st, a, groups);
+    case 408: return go<MODE, 4, 4, 8, true>(st, a, groups);
     case 801: return go<MODE, 8, 4, 1, true>(st, a, groups);
+    case 802: return go<MODE, 8, 4, 2, true>(st, a, groups);
     case 804: return go<MODE, 8, 4, 4, true>(st, a, groups);
     case 1601: return go<MODE, 16, 2, 1, true>(st, a, groups);
     case 1602: return go<MODE, 16, 2, 2, true>(st, a, groups);
@@ -525,9 +532,11 @@ PcgShape pcg_shape(int64_t s, int64_t k) {
   h.cpl = chunks <= 1 ? 1 : chunks <= 2 ? 2 : chunks <= 4 ? 4 : chunks <= 8 ? 8 : 16;
   const int rpw = h.cpl == 1 ? 8 : h.cpl == 2 ? 16 : h.cpl == 16 ? 2 : 4;
   h.nblk = (int)((s + NWV * rpw - 1) / (NWV * rpw));
-  // one column per group while the groups fit one launch, else four (two where four columns'
-  // vectors do not fit the registers beside the operands)
-  h.kc = (h.cpl <= 2 || k * h.nblk <= kPcgMaxBlocks) ? 1 : (h.cpl == 16 ? 2 : 4);
+  // the fewest columns per group (1, 2, 4, 8) with which the groups fit one launch; at most
+  // what the registers hold beside the operands (8 for s <= 256, 4 for s <= 512, else 2)
+  const int most = h.cpl <= 2 ? 1 : (h.cpl == 4 ? 8 : (h.cpl == 8 ? 4 : 2));
+  h.kc = 1;
+  while (h.kc < most && (k + h.kc - 1) / h.kc * h.nblk > kPcgMaxBlocks) h.kc *= 2;
   const int per = kPcgMaxBlocks / h.nblk > 0 ? kPcgMaxBlocks / h.nblk : 1;  // groups per launch
   h.groups = (int)((k + h.kc - 1) / h.kc);
   h.launches = (h.groups + per - 1) / per;
@@ -565,8 +574,8 @@ hipError_t pcg_reset(hipStream_t st, PcgRun& R) {
 hipError_t pcg_solve(hipStream_t st, PcgRun& R, PcgArgs a, int mode) {
   const PcgShape& h = R.shape;
   if (h.cpl == 0 || a.max_iter < 1 || a.max_iter > kPcgMaxIter) return hipErrorInvalidValue;
-  // exchanges of one launch: two per step and solve, and one spare
-  const uint64_t span = (uint64_t)a.nsol * (2 * (uint64_t)a.max_iter + 2);
+  // exchange numbers of one launch: two per step, the first and the unreceived last product
+  const uint64_t span = (uint64_t)a.nsol * (2 * (uint64_t)a.max_iter + 4);
   a.s = R.s;
   a.k = R.k;
   a.nblk = h.nblk;
