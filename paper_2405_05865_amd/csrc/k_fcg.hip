@@ -1,9 +1,17 @@
 // Flexible PCG (Polak-Ribiere beta) as a device-resident state machine. Each level
 // of the method (Algorithm 1/3 level 1, Algorithms 2/4 level 2, Algorithm 5 level 3)
-// runs the same five kernels on its own vectors and scalars; no host round trip is
+// runs the same kernels on its own vectors and scalars; no host round trip is
 // needed per step. Column j of a block iterates independently and stops on its own
 // residual; finished columns are skipped by every kernel.
+//
+// Every kernel here moves little data and is bound by latency: launch, one or two dependent
+// memory round trips, a block reduction. So the scalar work over k columns runs a wavefront
+// per column (a loop over the columns took 20 us with 16 and 54 us with 64), no kernel hands
+// over to its last block through device-scope fences (k_init took 9 to 53 us), the beta of a
+// step is summed by every block of the kernel that uses it, and short vectors (kShortLen,
+// kShortAll) take a whole update, and a whole direction, in one block.
 #include "msp_internal.h"
+#include "wave_ops.h"
 
 #include <algorithm>
 
@@ -12,11 +20,10 @@ namespace {
 constexpr int NT = 256;
 constexpr int WAVE = 64;
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-  return v;
-}
+using wave_ops::wave_sum;
+
+constexpr int NTD = 1024;       // threads of the one-block scalar kernels: a wavefront per column
+constexpr int NWD = NTD / WAVE;
 
 // sum of v over the block (valid in thread 0)
 __device__ __forceinline__ double block_sum(double v, double* sh) {
@@ -45,23 +52,9 @@ __device__ __forceinline__ double block_sum_all(double v, double* sh) {
   return t;
 }
 
-// true in every thread of the last block of the grid to reach this point
-__device__ __forceinline__ bool last_block(int32_t* counter) {
-  __shared__ int is_last;
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int total = gridDim.x * gridDim.y;
-    const int t = atomicAdd(counter, 1);
-    is_last = (t == total - 1);
-  }
-  __syncthreads();
-  if (is_last) __threadfence();
-  return is_last != 0;
-}
-
+// the active count and the most iterations, called by all NTD threads of a one-block kernel
+// after the columns' decisions
 __device__ __forceinline__ void count_active(FcgState S, int32_t* mirror) {
-  // called by the last block; all threads participate
   __shared__ int cnt, mx;
   if (threadIdx.x == 0) {
     cnt = 0;
@@ -69,12 +62,14 @@ __device__ __forceinline__ void count_active(FcgState S, int32_t* mirror) {
   }
   __syncthreads();
   int mine = 0, it = 0;
-  for (int64_t j = threadIdx.x; j < S.k; j += NT) {
+  for (int64_t j = threadIdx.x; j < S.k; j += NTD) {
     mine += (S.done[j] == 0);
     it = max(it, S.iters[j]);
   }
-  atomicAdd(&cnt, mine);
-  atomicMax(&mx, it);
+  if (threadIdx.x < S.k) {
+    atomicAdd(&cnt, mine);
+    atomicMax(&mx, it);
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     *S.active = cnt;
@@ -84,15 +79,24 @@ __device__ __forceinline__ void count_active(FcgState S, int32_t* mirror) {
       __hip_atomic_store(mirror, cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       __hip_atomic_store(mirror + 1, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    *S.counter = 0;
   }
 }
 
-// fixed-order parallel sum of part[b * stride] over b < count; valid in every thread
-__device__ __forceinline__ double strided_sum(const double* base, int count, int64_t stride, double* sh) {
+// sum of base[b * stride] over b < count by one wavefront in a fixed order, valid in its lanes
+__device__ __forceinline__ double wave_strided(const double* base, int count, int64_t stride) {
+  const int lane = threadIdx.x % WAVE;
   double t = 0.0;
-  for (int b = threadIdx.x; b < count; b += NT) t += base[(int64_t)b * stride];
-  return block_sum_all(t, sh);
+  for (int b0 = 0; b0 < count; b0 += 4 * WAVE) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int b = b0 + u * WAVE + lane;
+      v[u] = b < count ? base[(int64_t)b * stride] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t += v[u];
+  }
+  return wave_sum(t);
 }
 
 __device__ __forceinline__ int64_t chunk_begin(int64_t len) {
@@ -106,7 +110,7 @@ __device__ __forceinline__ int64_t chunk_end(int64_t len) {
 
 __global__ void __launch_bounds__(NT) k_init(FcgState S, int64_t len, const double* __restrict__ b, int64_t ldb,
                                             double* __restrict__ r, double* __restrict__ x,
-                                            const int32_t* __restrict__ parent_done, int32_t* mirror) {
+                                            const int32_t* __restrict__ parent_done) {
   __shared__ double sh[NT / WAVE];
   const int j = blockIdx.y;
   const bool pd = parent_done && parent_done[j] != 0;
@@ -119,10 +123,14 @@ __global__ void __launch_bounds__(NT) k_init(FcgState S, int64_t len, const doub
   }
   const double t = block_sum(acc, sh);
   if (threadIdx.x == 0) S.part[(int64_t)blockIdx.x * S.k + j] = t;
-  if (!last_block(S.counter)) return;
-  for (int64_t jj = 0; jj < S.k; ++jj) {
-    const double sum = strided_sum(S.part + jj, gridDim.x, S.k, sh);
-    if (threadIdx.x != 0) continue;
+}
+
+// |b| and the first decision from the partials of k_init
+__global__ void __launch_bounds__(NTD) k_init_fin(FcgState S, int nblocks, const int32_t* __restrict__ parent_done,
+                                                  int32_t* mirror) {
+  for (int jj = threadIdx.x / WAVE; jj < S.k; jj += NWD) {
+    const double sum = wave_strided(S.part + jj, nblocks, S.k);
+    if (threadIdx.x % WAVE != 0) continue;
     const double bn = sqrt(sum);
     const bool p = parent_done && parent_done[jj] != 0;
     S.bnorm[jj] = bn;
@@ -152,29 +160,13 @@ __global__ void __launch_bounds__(NT) k_first_dir(FcgState S, int64_t len, const
     }
   const double t = block_sum(acc, sh);
   if (threadIdx.x == 0) S.part[(int64_t)blockIdx.x * S.k + j] = t;
-  if (!last_block(S.counter)) return;
-  for (int64_t jj = 0; jj < S.k; ++jj) {
-    if (S.done[jj] != 0) continue;
-    const double sum = strided_sum(S.part + jj, gridDim.x, S.k, sh);
-    if (threadIdx.x == 0) S.rz[jj] = sum;
-  }
-  if (threadIdx.x == 0) *S.counter = 0;
 }
 
-__global__ void k_alpha_parts(FcgState S, const double* __restrict__ pq_part, int nparts) {
-  for (int64_t j = threadIdx.x; j < S.k; j += blockDim.x) {
-    if (S.done[j] != 0) {
-      S.alpha[j] = 0.0;
-      continue;
-    }
-    double pq = 0.0;
-    for (int b = 0; b < nparts; ++b) pq += pq_part[(int64_t)b * S.k + j];
-    if (!(pq > 0.0)) {
-      S.done[j] = 2;
-      S.alpha[j] = 0.0;
-    } else {
-      S.alpha[j] = S.rz[j] / pq;
-    }
+__global__ void __launch_bounds__(NTD) k_rz_fin(FcgState S, int nblocks) {
+  for (int jj = threadIdx.x / WAVE; jj < S.k; jj += NWD) {
+    if (S.done[jj] != 0) continue;
+    const double sum = wave_strided(S.part + jj, nblocks, S.k);
+    if (threadIdx.x % WAVE == 0) S.rz[jj] = sum;
   }
 }
 
@@ -238,17 +230,20 @@ __global__ void __launch_bounds__(NT) k_update(FcgState S, int64_t len, double* 
   if (threadIdx.x == 0) S.part[(int64_t)blockIdx.x * S.k + j] = t;
 }
 
-// the decision after k_update, in one block (a separate launch instead of a last-block
+// breakdown markers of k_decide: none, brk[] from the partial dots, alpha == 0 (set by the
+// step length when <p, q> <= 0)
+enum { BRK_NONE = 0, BRK_FLAG = 1, BRK_ALPHA = 2 };
+
+// the decision after an update, in one block (a separate launch instead of a last-block
 // hand-off: a device-scope fence in every block of the update costs more than a launch):
 // |r| from the nblocks partials, breakdown, tolerance, iteration cap; mirror <- active
-__global__ void __launch_bounds__(NT) k_decide(FcgState S, int nblocks, double tol, int32_t max_iter,
-                                              int32_t* mirror, int check_brk) {
-  __shared__ double sh[NT / WAVE];
-  for (int64_t jj = 0; jj < S.k; ++jj) {
-    if (S.done[jj] != 0) continue;  // uniform in the block
-    const double sum = strided_sum(S.part + jj, nblocks, S.k, sh);
-    if (threadIdx.x != 0) continue;
-    if (check_brk && S.brk[jj]) {
+__global__ void __launch_bounds__(NTD) k_decide(FcgState S, int nblocks, double tol, int32_t max_iter,
+                                               int32_t* mirror, int brk) {
+  for (int jj = threadIdx.x / WAVE; jj < S.k; jj += NWD) {
+    if (S.done[jj] != 0) continue;  // uniform in the wavefront
+    const double sum = wave_strided(S.part + jj, nblocks, S.k);
+    if (threadIdx.x % WAVE != 0) continue;
+    if (brk == BRK_FLAG && S.brk[jj]) {
       S.done[jj] = 2;
       continue;
     }
@@ -256,7 +251,7 @@ __global__ void __launch_bounds__(NT) k_decide(FcgState S, int nblocks, double t
     S.rnorm[jj] = rn;
     const int it = S.iters[jj] + 1;
     S.iters[jj] = it;
-    if (!(rn == rn)) S.done[jj] = 2;  // NaN
+    if (!(rn == rn) || (brk == BRK_ALPHA && S.alpha[jj] == 0.0)) S.done[jj] = 2;  // NaN or breakdown
     else if (rn <= tol * S.bnorm[jj]) S.done[jj] = 1;
     else if (it >= max_iter) S.done[jj] = 3;
   }
@@ -285,44 +280,39 @@ __global__ void __launch_bounds__(NT) k_beta(FcgState S, int64_t len, const doub
   }
 }
 
-// beta = <z, r - r_old> / rz and rz = <z, r> from the partials of k_beta, in one block (a
-// separate launch instead of a fenced last-block hand-off). When the denominator
+// beta = <z, r - r_old> / rz from the partials of k_beta, summed by every block of the column
+// in the same order, then p = z + beta p. The new rz = <z, r> goes to rz_next (other blocks
+// still read rz); the host exchanges the two pointers after the launch. When the denominator
 // rz = <r_old, z_old> is zero or not finite no conjugate direction exists (an inexact
 // preconditioner that is not positive definite): the column stops as a breakdown and
-// keeps its iterate; k_pupdate then leaves p alone and the next decision recounts the
-// active columns.
-__global__ void __launch_bounds__(NT) k_beta_fin(FcgState S, int nblocks) {
-  __shared__ double sh[NT / WAVE];
-  for (int64_t jj = 0; jj < S.k; ++jj) {
-    if (S.done[jj] != 0) continue;
-    const double zr = strided_sum(S.part + jj * 2 + 0, nblocks, S.k * 2, sh);
-    const double zro = strided_sum(S.part + jj * 2 + 1, nblocks, S.k * 2, sh);
-    if (threadIdx.x == 0) {
-      const double rz = S.rz[jj];
-      if (rz != 0.0 && isfinite(rz)) {
-        S.beta[jj] = (zr - zro) / rz;
-        S.rz[jj] = zr;
-      } else {
-        S.beta[jj] = 0.0;
-        S.done[jj] = 2;
-      }
-    }
-  }
-}
-
+// keeps its iterate and p; the next decision recounts the active columns.
 __global__ void __launch_bounds__(NT) k_pupdate(FcgState S, int64_t len, const double* __restrict__ z,
-                                               double* __restrict__ p) {
-  const int j = blockIdx.y;
-  if (S.done[j] != 0) return;
-  const double bt = S.beta[j];
+                                               double* __restrict__ p, int nblocks) {
+  __shared__ double sh[2];
+  const int j = blockIdx.y, w = threadIdx.x / WAVE;
+  const double rz = S.rz[j];
+  const bool live = S.done[j] == 0;
+  if (w < 2) {
+    const double t = wave_strided(S.part + j * 2 + w, nblocks, S.k * 2);
+    if (threadIdx.x % WAVE == 0) sh[w] = t;
+  }
+  __syncthreads();
+  const double zr = sh[0], zro = sh[1];
+  const bool ok = live && rz != 0.0 && isfinite(rz);
+  const double bt = ok ? (zr - zro) / rz : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S.rz_next[j] = ok ? zr : rz;
+    S.beta[j] = bt;
+    if (live && !ok) S.done[j] = 2;  // (the other blocks leave p alone either way: ok is false)
+  }
+  if (!ok) return;
   for (int64_t i = chunk_begin(len) + threadIdx.x; i < chunk_end(len); i += NT) {
     const int64_t o = (int64_t)j * len + i;
     p[o] = fma(bt, p[o], z[o]);
   }
 }
 
-__global__ void __launch_bounds__(NT) k_confirm(FcgState S, int64_t len, const double* __restrict__ rtrue,
-                                               double* __restrict__ r, double tol, double* relres, int32_t* mirror) {
+__global__ void __launch_bounds__(NT) k_confirm(FcgState S, int64_t len, const double* __restrict__ rtrue) {
   __shared__ double sh[NT / WAVE];
   const int j = blockIdx.y;
   double acc = 0.0;
@@ -332,13 +322,14 @@ __global__ void __launch_bounds__(NT) k_confirm(FcgState S, int64_t len, const d
   }
   const double t = block_sum(acc, sh);
   if (threadIdx.x == 0) S.part[(int64_t)blockIdx.x * S.k + j] = t;
-  __shared__ int restart;
-  const bool last = last_block(S.counter);
-  if (!last) return;
-  __syncthreads();
-  for (int64_t jj = 0; jj < S.k; ++jj) {
-    const double sum = strided_sum(S.part + jj, gridDim.x, S.k, sh);
-    if (threadIdx.x != 0) continue;
+}
+
+__global__ void __launch_bounds__(NTD) k_confirm_fin(FcgState S, int nblocks, int64_t len,
+                                                     const double* __restrict__ rtrue, double* __restrict__ r,
+                                                     double tol, double* relres, int32_t* mirror) {
+  for (int jj = threadIdx.x / WAVE; jj < S.k; jj += NWD) {
+    const double sum = wave_strided(S.part + jj, nblocks, S.k);
+    if (threadIdx.x % WAVE != 0) continue;
     const double bn = S.bnorm[jj];
     const double rel = bn > 0.0 ? sqrt(sum) / bn : 0.0;
     relres[jj] = rel;
@@ -346,14 +337,183 @@ __global__ void __launch_bounds__(NT) k_confirm(FcgState S, int64_t len, const d
   }
   __syncthreads();
   // restarted columns take the recomputed residual
-  (void)restart;
   for (int64_t jj = 0; jj < S.k; ++jj) {
     if (S.done[jj] != 0) continue;
-    for (int64_t i = threadIdx.x; i < len; i += NT) r[jj * len + i] = rtrue[jj * len + i];
+    for (int64_t i = threadIdx.x; i < len; i += NTD) r[jj * len + i] = rtrue[jj * len + i];
   }
   __syncthreads();
   count_active(S, mirror);
 }
+
+// ---- short vectors: one block, G wavefronts per column (16 for one column, 1 from 16 on) ----
+// G wavefronts share a column's elements; their sums meet in LDS. Every thread takes the same
+// rounds, so the barriers are uniform.
+struct ShortGroup {
+  int G, per, rounds;  // wavefronts per column, columns per round, rounds
+  __device__ ShortGroup(int k, int len) {
+    G = k > 8 ? 1 : (k > 4 ? 2 : (k > 2 ? 4 : (k > 1 ? 8 : 16)));
+    while (G > 1 && G / 2 * WAVE >= len) G /= 2;  // no wavefront without elements
+    per = NWD / G;
+    rounds = (k + per - 1) / per;
+  }
+  // sum of v over the group's lanes, valid in all of them
+  __device__ double sum(double v, double* sh) const {
+    v = wave_sum(v);
+    if (G == 1) return v;
+    const int w = threadIdx.x / WAVE;
+    __syncthreads();
+    if (threadIdx.x % WAVE == 0) sh[w] = v;
+    __syncthreads();
+    const int w0 = w / G * G;
+    double t = 0.0;
+    for (int q = 0; q < G; ++q) t += sh[w0 + q];
+    return t;
+  }
+};
+
+// One launch for q += c t (t may be null), alpha = rz / <p, q>, x += alpha p, r_old = r,
+// r -= alpha q and the decision on |r|. s = 512, 8 columns: the axpby, k_alpha_dot, k_update
+// and k_decide took 24 us, this 8.8 us.
+__global__ void __launch_bounds__(NTD) k_short_step(FcgState S, int len, double* __restrict__ x, double* __restrict__ r,
+                                                   double* __restrict__ r_old, const double* __restrict__ p,
+                                                   double* __restrict__ q, double c, const double* __restrict__ t,
+                                                   double tol, int32_t max_iter, int32_t* mirror) {
+  constexpr int U = 4;
+  __shared__ double sh[NWD];
+  const ShortGroup grp((int)S.k, len);
+  const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+  const int l0 = (w % grp.G) * WAVE + lane, step = grp.G * WAVE;
+  for (int rd = 0; rd < grp.rounds; ++rd) {
+    const int j = rd * grp.per + w / grp.G;
+    const bool live = j < S.k && S.done[min(j, (int)S.k - 1)] == 0;
+    const int64_t o = (int64_t)j * len;
+    double pq = 0.0;
+    double pv[U], qv[U], rv[U], xv[U];
+    for (int i0 = 0; live && i0 < len; i0 += U * step) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * step + l0;
+        const bool in = i < len;
+        pv[u] = in ? p[o + i] : 0.0;
+        qv[u] = in ? q[o + i] : 0.0;
+        rv[u] = in ? r[o + i] : 0.0;
+        xv[u] = in ? x[o + i] : 0.0;
+        if (t && in) {
+          qv[u] = fma(c, t[o + i], qv[u]);
+          if (len > U * step) q[o + i] = qv[u];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) pq = fma(pv[u], qv[u], pq);
+    }
+    pq = grp.sum(pq, sh);
+    const bool brk = !(pq > 0.0);
+    const double a = (brk || !live) ? 0.0 : S.rz[j] / pq;
+    double rr = 0.0;
+    for (int i0 = 0; live && i0 < len; i0 += U * step) {
+      if (len > U * step) {  // otherwise the values are still in registers
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * step + l0;
+          const bool in = i < len;
+          pv[u] = in ? p[o + i] : 0.0;
+          qv[u] = in ? q[o + i] : 0.0;
+          rv[u] = in ? r[o + i] : 0.0;
+          xv[u] = in ? x[o + i] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * step + l0;
+        if (i >= len) continue;
+        x[o + i] = fma(a, pv[u], xv[u]);
+        r_old[o + i] = rv[u];
+        const double rn = fma(-a, qv[u], rv[u]);
+        r[o + i] = rn;
+        rr = fma(rn, rn, rr);
+      }
+    }
+    rr = grp.sum(rr, sh);
+    if (lane == 0 && w % grp.G == 0 && j < S.k) {
+      S.alpha[j] = a;
+      if (live && brk) {
+        S.done[j] = 2;
+      } else if (live) {
+        const double rn = sqrt(rr);
+        S.rnorm[j] = rn;
+        const int it = S.iters[j] + 1;
+        S.iters[j] = it;
+        if (!(rn == rn)) S.done[j] = 2;
+        else if (rn <= tol * S.bnorm[j]) S.done[j] = 1;
+        else if (it >= max_iter) S.done[j] = 3;
+      }
+    }
+  }
+  __syncthreads();
+  count_active(S, mirror);
+}
+
+// beta, rz and p = z + beta p in one launch (k_beta and k_pupdate: 8 us)
+__global__ void __launch_bounds__(NTD) k_short_dir(FcgState S, int len, const double* __restrict__ r,
+                                                  const double* __restrict__ r_old, const double* __restrict__ z,
+                                                  double* __restrict__ p) {
+  constexpr int U = 4;
+  __shared__ double sh[NWD];
+  const ShortGroup grp((int)S.k, len);
+  const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+  const int l0 = (w % grp.G) * WAVE + lane, step = grp.G * WAVE;
+  for (int rd = 0; rd < grp.rounds; ++rd) {
+    const int j = rd * grp.per + w / grp.G;
+    const bool live = j < S.k && S.done[min(j, (int)S.k - 1)] == 0;
+    const double rz = live ? S.rz[j] : 1.0;
+    const int64_t o = (int64_t)j * len;
+    double zr = 0.0, zro = 0.0;
+    double zv[U], pv[U];
+    for (int i0 = 0; live && i0 < len; i0 += U * step) {
+      double rv[U], ov[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * step + l0;
+        const bool in = i < len;
+        zv[u] = in ? z[o + i] : 0.0;
+        rv[u] = in ? r[o + i] : 0.0;
+        ov[u] = in ? r_old[o + i] : 0.0;
+        pv[u] = in ? p[o + i] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        zr = fma(zv[u], rv[u], zr);
+        zro = fma(zv[u], ov[u], zro);
+      }
+    }
+    zr = grp.sum(zr, sh);
+    zro = grp.sum(zro, sh);
+    const bool ok = live && rz != 0.0 && isfinite(rz);  // otherwise as in k_pupdate: a breakdown, p is left alone
+    const double bt = ok ? (zr - zro) / rz : 0.0;
+    for (int i0 = 0; ok && i0 < len; i0 += U * step) {
+      if (len > U * step) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * step + l0;
+          zv[u] = i < len ? z[o + i] : 0.0;
+          pv[u] = i < len ? p[o + i] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * step + l0;
+        if (i < len) p[o + i] = fma(bt, pv[u], zv[u]);
+      }
+    }
+    if (live && lane == 0 && w % grp.G == 0) {
+      S.beta[j] = bt;
+      if (ok) S.rz[j] = zr;
+      else S.done[j] = 2;
+    }
+  }
+}
+
+bool is_short(int64_t len, int64_t k) { return len <= kShortLen && len * k <= kShortAll; }
 
 __global__ void k_axpby(int64_t len, int k, double a, const double* __restrict__ x, int64_t ldx, double b,
                         const double* __restrict__ y, int64_t ldy, double* __restrict__ out, int64_t ldo,
@@ -443,6 +603,7 @@ FcgState carve_fcg_state(WsCarver& w, int64_t len, int64_t k) {
   FcgState S;
   S.k = k;
   S.rz = w.take<double>(k);
+  S.rz_next = w.take<double>(k);
   S.alpha = w.take<double>(k);
   S.beta = w.take<double>(k);
   S.bnorm = w.take<double>(k);
@@ -460,16 +621,13 @@ FcgState carve_fcg_state(WsCarver& w, int64_t len, int64_t k) {
 
 hipError_t fcg_init(hipStream_t st, FcgState S, int64_t len, const double* b, int64_t ldb, double* r, double* x,
                     const int32_t* parent_done, int32_t* mirror) {
-  hipLaunchKernelGGL(k_init, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, b, ldb, r, x, parent_done,
-                     mirror);
+  hipLaunchKernelGGL(k_init, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, b, ldb, r, x, parent_done);
+  hipLaunchKernelGGL(k_init_fin, dim3(1), dim3(NTD), 0, st, S, (int)grid_x(len), parent_done, mirror);
   return hipGetLastError();
 }
 hipError_t fcg_first_dir(hipStream_t st, FcgState S, int64_t len, const double* r, const double* z, double* p) {
   hipLaunchKernelGGL(k_first_dir, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, r, z, p);
-  return hipGetLastError();
-}
-hipError_t fcg_alpha_parts(hipStream_t st, FcgState S, const double* pq_part, int nparts) {
-  hipLaunchKernelGGL(k_alpha_parts, dim3(1), dim3(NT), 0, st, S, pq_part, nparts);
+  hipLaunchKernelGGL(k_rz_fin, dim3(1), dim3(NTD), 0, st, S, (int)grid_x(len));
   return hipGetLastError();
 }
 hipError_t fcg_alpha_dot(hipStream_t st, FcgState S, int64_t len, const double* p, const double* q) {
@@ -481,9 +639,22 @@ hipError_t fcg_update(hipStream_t st, FcgState S, int64_t len, double* x, double
                       int nparts) {
   hipLaunchKernelGGL(k_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, x, r, r_old, p, q, tol,
                      max_iter, mirror, pq_part, nparts, 1);
-  hipLaunchKernelGGL(k_decide, dim3(1), dim3(NT), 0, st, S, (int)grid_x(len), tol, max_iter, mirror,
-                     pq_part ? 1 : 0);
+  hipLaunchKernelGGL(k_decide, dim3(1), dim3(NTD), 0, st, S, (int)grid_x(len), tol, max_iter, mirror,
+                     pq_part ? BRK_FLAG : BRK_NONE);
   return hipGetLastError();
+}
+hipError_t fcg_step(hipStream_t st, FcgState S, int64_t len, double* x, double* r, double* r_old, const double* p,
+                    double* q, double c, const double* t, double tol, int32_t max_iter, int32_t* mirror) {
+  if (is_short(len, S.k)) {
+    hipLaunchKernelGGL(k_short_step, dim3(1), dim3(NTD), 0, st, S, (int)len, x, r, r_old, p, q, c, t, tol, max_iter,
+                       mirror);
+    return hipGetLastError();
+  }
+  hipError_t e = hipSuccess;
+  if (t) e = launch_axpby(st, len, S.k, 1.0, q, len, c, t, len, q, len, S.done);
+  if (e == hipSuccess) e = fcg_alpha_dot(st, S, len, p, q);
+  if (e == hipSuccess) e = fcg_update(st, S, len, x, r, r_old, p, q, tol, max_iter, mirror);
+  return e;
 }
 
 // the same update without the convergence decision (the general path decides on rho)
@@ -497,8 +668,7 @@ hipError_t fcg_update_nodecide(hipStream_t st, FcgState S, int64_t len, double* 
 // rho -= alpha t (the residual of A x = b carried next to the normal-equation residual);
 // the decision (tol, cap, NaN, breakdown) is taken on |rho|
 __global__ void __launch_bounds__(NT) k_rho_update(FcgState S, int64_t len, double* __restrict__ rho,
-                                                  const double* __restrict__ t, double tol, int32_t max_iter,
-                                                  int32_t* mirror) {
+                                                  const double* __restrict__ t) {
   __shared__ double sh[NT / WAVE];
   const int j = blockIdx.y;
   double acc = 0.0;
@@ -513,50 +683,30 @@ __global__ void __launch_bounds__(NT) k_rho_update(FcgState S, int64_t len, doub
   }
   const double tt = block_sum(acc, sh);
   if (threadIdx.x == 0) S.part[(int64_t)blockIdx.x * S.k + j] = tt;
-  if (!last_block(S.counter)) return;
-  for (int64_t jj = 0; jj < S.k; ++jj) {
-    if (S.done[jj] != 0) continue;
-    const double sum = strided_sum(S.part + jj, gridDim.x, S.k, sh);
-    if (threadIdx.x != 0) continue;
-    const double rn = sqrt(sum);
-    S.rnorm[jj] = rn;
-    const int it = S.iters[jj] + 1;
-    S.iters[jj] = it;
-    if (S.alpha[jj] == 0.0 || !(rn == rn)) S.done[jj] = 2;
-    else if (rn <= tol * S.bnorm[jj]) S.done[jj] = 1;
-    else if (it >= max_iter) S.done[jj] = 3;
-  }
-  __syncthreads();
-  count_active(S, mirror);
 }
 
 hipError_t fcg_rho_update(hipStream_t st, FcgState S, int64_t len, double* rho, const double* t, double tol,
                           int32_t max_iter, int32_t* mirror) {
-  hipLaunchKernelGGL(k_rho_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, rho, t, tol, max_iter,
-                     mirror);
+  hipLaunchKernelGGL(k_rho_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, rho, t);
+  hipLaunchKernelGGL(k_decide, dim3(1), dim3(NTD), 0, st, S, (int)grid_x(len), tol, max_iter, mirror, BRK_ALPHA);
   return hipGetLastError();
 }
 
-// done = 0 for columns whose done flag equals `from` (restart after a failed confirmation
-// is handled by k_confirm; this re-arms columns for a fresh solve)
-__global__ void k_set_done(FcgState S, const int32_t* src) {
-  for (int64_t j = threadIdx.x; j < S.k; j += blockDim.x) S.done[j] = src ? src[j] : 0;
-}
-hipError_t fcg_copy_done(hipStream_t st, FcgState S, const int32_t* src) {
-  hipLaunchKernelGGL(k_set_done, dim3(1), dim3(256), 0, st, S, src);
-  return hipGetLastError();
-}
-hipError_t fcg_direction(hipStream_t st, FcgState S, int64_t len, const double* r, const double* r_old,
+hipError_t fcg_direction(hipStream_t st, FcgState& S, int64_t len, const double* r, const double* r_old,
                          const double* z, double* p) {
+  if (is_short(len, S.k)) {
+    hipLaunchKernelGGL(k_short_dir, dim3(1), dim3(NTD), 0, st, S, (int)len, r, r_old, z, p);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_beta, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, r, r_old, z);
-  hipLaunchKernelGGL(k_beta_fin, dim3(1), dim3(NT), 0, st, S, (int)grid_x(len));
-  hipLaunchKernelGGL(k_pupdate, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, z, p);
+  hipLaunchKernelGGL(k_pupdate, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, z, p, (int)grid_x(len));
+  std::swap(S.rz, S.rz_next);
   return hipGetLastError();
 }
 hipError_t fcg_confirm(hipStream_t st, FcgState S, int64_t len, const double* rtrue, double* r, double tol,
                        double* relres, int32_t* mirror) {
-  hipLaunchKernelGGL(k_confirm, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, rtrue, r, tol, relres,
-                     mirror);
+  hipLaunchKernelGGL(k_confirm, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, rtrue);
+  hipLaunchKernelGGL(k_confirm_fin, dim3(1), dim3(NTD), 0, st, S, (int)grid_x(len), len, rtrue, r, tol, relres, mirror);
   return hipGetLastError();
 }
 hipError_t launch_axpby(hipStream_t st, int64_t len, int64_t k, double a, const double* x, int64_t ldx, double b,

@@ -724,6 +724,12 @@ hipError_t prec_launch(hipStream_t st, const L2Step& a, int decide) {
 
 }  // namespace
 
+const double* l2_groups(const L2Step& a, int* ng) {
+  *ng = ngroups(a.nbC);
+  return a.part + (size_t)a.nbC * a.k * a.s;
+}
+
+
 int l2_blocks(int64_t n) {
   int64_t b = (n + 31) / 32;
   if (b > 1024) b = 1024;

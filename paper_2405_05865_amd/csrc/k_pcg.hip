@@ -258,6 +258,10 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
   double v2[2][EPT], v1[1][EPT];
 #pragma unroll
   for (int q = 0; q < EPT; ++q) y[q] = ein[q] ? a.rhs[eo[q]] : 0.0;
+  for (int g = 1; g < a.nrhs; ++g)
+#pragma unroll
+    for (int q = 0; q < EPT; ++q)
+      if (ein[q]) y[q] += a.rhs[(int64_t)g * a.k * s + eo[q]];
 
   auto stage = [&](const double(&x)[EPT]) {
 #pragma unroll
@@ -576,6 +580,7 @@ hipError_t pcg_solve(hipStream_t st, PcgRun& R, PcgArgs a, int mode) {
   if (h.cpl == 0 || a.max_iter < 1 || a.max_iter > kPcgMaxIter) return hipErrorInvalidValue;
   // exchange numbers of one launch: two per step, the first and the unreceived last product
   const uint64_t span = (uint64_t)a.nsol * (2 * (uint64_t)a.max_iter + 4);
+  if (a.nrhs < 1) a.nrhs = 1;
   a.s = R.s;
   a.k = R.k;
   a.nblk = h.nblk;

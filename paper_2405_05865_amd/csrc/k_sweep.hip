@@ -7,6 +7,8 @@
 
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
+
 namespace {
 
 constexpr int WAVE = 64;
@@ -185,11 +187,15 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
   }
 }
 
-// Y[:, j] = A^T X[:, j]: block (column tile, row tile); partial over the row tile
+// Y[:, j] = A^T X[:, j]: block (column tile, row tile); partial over the row tile, or with one
+// row tile the result itself (direct). Eight rows' loads are in flight per thread: the short
+// products of the inner levels (s rows) are one or a few such rounds.
 template <class TA, class TC, int VEC, int K>
 __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t lda, int64_t rows, int64_t cols,
                                               const double* __restrict__ X, int64_t ldx, int k, int j0,
-                                              int64_t rows_per_tile, double* __restrict__ part) {
+                                              int64_t rows_per_tile, double* __restrict__ out, int64_t ldo,
+                                              const int32_t* __restrict__ skip, int direct) {
+  constexpr int U = K >= 4 ? 4 : 8;
   const int64_t c = ((int64_t)blockIdx.x * NT + threadIdx.x) * VEC;
   const int64_t rb = (int64_t)blockIdx.y * rows_per_tile;
   const int64_t re = min(rows, rb + rows_per_tile);
@@ -199,7 +205,25 @@ __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[j][v] = (TC)0;
   const bool full = (c + VEC <= cols);
-  for (int64_t r = rb; r < re; ++r) {
+  auto add = [&](int64_t r, const TC(&a)[VEC]) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      const TC x = (j0 + j < k) ? (TC)X[(int64_t)(j0 + j) * ldx + r] : (TC)0;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[j][v] = fma(a[v], x, acc[j][v]);
+    }
+  };
+  int64_t r = rb;
+  if (full) {
+    for (; r + U <= re; r += U) {
+      TC a[U][VEC];
+#pragma unroll
+      for (int u = 0; u < U; ++u) Vec16<TA, TC, VEC>::load(A + (r + u) * lda + c, a[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) add(r + u, a[u]);
+    }
+  }
+  for (; r < re; ++r) {
     TC a[VEC];
     if (full) {
       Vec16<TA, TC, VEC>::load(A + r * lda + c, a);
@@ -207,20 +231,16 @@ __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t
 #pragma unroll
       for (int v = 0; v < VEC; ++v) a[v] = (c + v < cols) ? scalar_as<TA, TC>(A + r * lda + c + v) : (TC)0;
     }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const TC x = (j0 + j < k) ? (TC)X[(int64_t)(j0 + j) * ldx + r] : (TC)0;
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) acc[j][v] = fma(a[v], x, acc[j][v]);
-    }
+    add(r, a);
   }
-  double* out = part + (int64_t)blockIdx.y * k * cols;
+  if (!direct) out += (int64_t)blockIdx.y * k * cols;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     if (j0 + j >= k) break;
+    if (direct && skip && skip[j0 + j]) continue;
 #pragma unroll
     for (int v = 0; v < VEC; ++v)
-      if (c + v < cols) out[(int64_t)(j0 + j) * cols + c + v] = (double)acc[j][v];
+      if (c + v < cols) out[(int64_t)(j0 + j) * ldo + c + v] = (double)acc[j][v];
   }
 }
 
@@ -233,7 +253,13 @@ __global__ void k_sum_tiles(const double* __restrict__ part, int tiles, int64_t 
   const int64_t c = i % cols;
   if (skip && skip[j]) return;
   double acc = 0.0;
-  for (int t = 0; t < tiles; ++t) acc += part[(int64_t)t * len + i];
+  for (int t0 = 0; t0 < tiles; t0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = t0 + u < tiles ? part[(int64_t)(t0 + u) * len + i] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += v[u];
+  }
   Y[(int64_t)j * ldy + c] = acc;
 }
 
@@ -262,19 +288,30 @@ hipError_t gemv_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
 template <class TA, class TC, int VEC>
 hipError_t gemvT_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X,
                    int64_t ldx, double* Y, int64_t ldy, int k, const int32_t* skip, double* part) {
-  constexpr int K = 4;
   const int64_t ctiles = (cols + (int64_t)NT * VEC - 1) / ((int64_t)NT * VEC);
+  // enough row tiles to fill the chip, of 32 rows or more (shorter ones cost more in partials
+  // than they win: 32 rows x 128 columns took 5 + 10 us as 32 tiles, 3.5 us as one)
   int64_t rtiles = (2048 + ctiles - 1) / ctiles;
-  if (rtiles > 64) rtiles = 64;
-  if (rtiles > rows) rtiles = rows;
+  rtiles = std::max<int64_t>(1, std::min<int64_t>(rtiles, std::min<int64_t>(64, rows / 32)));
   const int64_t rpt = (rows + rtiles - 1) / rtiles;
   rtiles = (rows + rpt - 1) / rpt;
-  for (int j0 = 0; j0 < k; j0 += K)
-    hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, K>), dim3((unsigned)ctiles, (unsigned)rtiles), dim3(NT), 0, st, A, lda,
-                       rows, cols, X, ldx, k, j0, rpt, part);
-  const int64_t len = cols * k;
-  hipLaunchKernelGGL(k_sum_tiles, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, part, (int)rtiles, cols, k,
-                     skip, Y, ldy);
+  const int direct = rtiles == 1;
+  double* out = direct ? Y : part;
+  const int64_t ldo = direct ? ldy : cols;
+  const dim3 grid((unsigned)ctiles, (unsigned)rtiles);
+  if (k == 1) {
+    hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, 1>), grid, dim3(NT), 0, st, A, lda, rows, cols, X, ldx, k, 0, rpt, out, ldo,
+                       skip, direct);
+  } else {
+    for (int j0 = 0; j0 < k; j0 += 4)
+      hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, 4>), grid, dim3(NT), 0, st, A, lda, rows, cols, X, ldx, k, j0, rpt, out,
+                         ldo, skip, direct);
+  }
+  if (!direct) {
+    const int64_t len = cols * k;
+    hipLaunchKernelGGL(k_sum_tiles, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, part, (int)rtiles, cols, k,
+                       skip, Y, ldy);
+  }
   return hipGetLastError();
 }
 

@@ -1106,12 +1106,11 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
     return MSP_OK;
   }
   if (c.use_p) {  // the whole solve in one launch, H applied through G2 = H M2^{-1}
-    MSP_CHECK_HIP(l2_reduce_to(c.st, a, c.rhs2, pdone));
     PcgArgs p{};
     p.H = c.G2;
     p.Minv[0] = P->Minv;
     p.nsol = 1;
-    p.rhs = c.rhs2;
+    p.rhs = l2_groups(a, &p.nrhs);
     p.out = c.L2.x;
     p.parent_done = pdone;
     p.tol = c.o->inner_tol;
@@ -1246,8 +1245,9 @@ msp_status gen_solve_m2(SolveCtx& c, const double* r, double* z, const int32_t* 
   return MSP_OK;
 }
 
-// q2 = A~^T A A^T A~ p2 + lam~ A~^T A~ p2   (the operator of Algorithm 4)
-msp_status gen_op2(SolveCtx& c, const double* p2, double* q2, const int32_t* skip) {
+// q2 + cq tq = A~^T A A^T A~ p2 + lam~ A~^T A~ p2   (the operator of Algorithm 4; tq may be
+// null: the step adds it to q2)
+msp_status gen_op2(SolveCtx& c, const double* p2, double* q2, const int32_t* skip, double* cq, const double** tq) {
   const msp_precond* P = c.P;
   const int64_t m = c.m, n = c.n, s = c.s, k = c.k;
   if (c.form == 1) {
@@ -1257,7 +1257,8 @@ msp_status gen_op2(SolveCtx& c, const double* p2, double* q2, const int32_t* ski
     TRY(dense_mv_t(c, c.B2t, s, n, p2, s, c.nvec, n, skip));
     TRY(dense_mv(c, c.B2t, s, n, c.nvec, n, q2, s, skip));
     TRY(dense_mv(c, c.H3, s, s, p2, s, c.tmp_s, s, skip));
-    MSP_CHECK_HIP(launch_axpby(c.st, s, k, 1.0, q2, s, P->lt, c.tmp_s, s, q2, s, skip));
+    *cq = P->lt;
+    *tq = c.tmp_s;
     return MSP_OK;
   }
   MSP_CHECK_HIP(launch_y_z(c.st, P->Y, P->y_t, m, s, P->ldy, p2, k, 0.0, nullptr, 0, 1.0, skip, c.mvec, m));
@@ -1299,9 +1300,11 @@ msp_status gen_solve_m1(SolveCtx& c, const double* r, double* z) {
   for (int it = 0; it < c.o->max_inner; ++it) {
     TRY(sync(c));
     if (*slot(c, SLOT_L2) == 0) break;
-    TRY(gen_op2(c, L.p, L.q, L.S.done));
-    MSP_CHECK_HIP(fcg_alpha_dot(c.st, L.S, s, L.p, L.q));
-    MSP_CHECK_HIP(fcg_update(c.st, L.S, s, L.x, L.r, L.ro, L.p, L.q, c.o->inner_tol, c.o->max_inner, c.df + SLOT_L2));
+    double cq = 0.0;
+    const double* tq = nullptr;
+    TRY(gen_op2(c, L.p, L.q, L.S.done, &cq, &tq));
+    MSP_CHECK_HIP(fcg_step(c.st, L.S, s, L.x, L.r, L.ro, L.p, L.q, cq, tq, c.o->inner_tol, c.o->max_inner,
+                           c.df + SLOT_L2));
     TRY(gen_solve_m2(c, L.r, L.z, L.S.done));
     MSP_CHECK_HIP(fcg_direction(c.st, L.S, s, L.r, L.ro, L.z, L.p));
   }
@@ -1367,10 +1370,10 @@ msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
     }
     if (it >= max_outer) break;
     TRY(gen_op1(c, L.p, L.q, c.tvec, L.S.done));
-    MSP_CHECK_HIP(fcg_alpha_dot(c.st, L.S, n, L.p, L.q));
     if (normal) {
-      MSP_CHECK_HIP(fcg_update(c.st, L.S, n, L.x, L.r, L.ro, L.p, L.q, tol, max_outer, c.df + SLOT_L1));
+      MSP_CHECK_HIP(fcg_step(c.st, L.S, n, L.x, L.r, L.ro, L.p, L.q, 0.0, nullptr, tol, max_outer, c.df + SLOT_L1));
     } else {
+      MSP_CHECK_HIP(fcg_alpha_dot(c.st, L.S, n, L.p, L.q));
       MSP_CHECK_HIP(fcg_update_nodecide(c.st, L.S, n, L.x, L.r, L.ro, L.p, L.q));
       MSP_CHECK_HIP(fcg_rho_update(c.st, L.S, m, c.rho, c.tvec, tol, max_outer, c.df + SLOT_L1));
     }

@@ -221,6 +221,7 @@ hipError_t launch_small_mv(hipStream_t st, int64_t s, const double* M, const dou
 // ---------------------------------------------------------------------------------
 struct FcgState {
   double* rz;
+  double* rz_next;   // the other of the two rz buffers (fcg_direction exchanges them)
   double* alpha;
   double* beta;
   double* bnorm;
@@ -242,8 +243,6 @@ hipError_t fcg_init(hipStream_t st, FcgState S, int64_t len, const double* b, in
                     const int32_t* parent_done, int32_t* mirror);
 // p = z, rz = <r, z>   (columns not done)
 hipError_t fcg_first_dir(hipStream_t st, FcgState S, int64_t len, const double* r, const double* z, double* p);
-// alpha = rz / pq with pq = sum of nparts per-block partials (layout part[b*k + j])
-hipError_t fcg_alpha_parts(hipStream_t st, FcgState S, const double* pq_part, int nparts);
 // alpha = rz / <p, q> computed directly (short vectors)
 hipError_t fcg_alpha_dot(hipStream_t st, FcgState S, int64_t len, const double* p, const double* q);
 // x += alpha p; r_old = r; r -= alpha q; |r| -> done by tol / max_iter; mirror <- active.
@@ -252,15 +251,20 @@ hipError_t fcg_alpha_dot(hipStream_t st, FcgState S, int64_t len, const double* 
 hipError_t fcg_update(hipStream_t st, FcgState S, int64_t len, double* x, double* r, double* r_old,
                       const double* p, const double* q, double tol, int32_t max_iter, int32_t* mirror,
                       const double* pq_part = nullptr, int nparts = 0);
+// q += c t (t may be null), alpha = rz / <p, q>, then fcg_update: one launch for vectors of at
+// most kShortLen elements, kShortAll over the columns (more is too much for one block: 42 us
+// for 64 columns of 2048, against 11 us on the whole chip)
+constexpr int64_t kShortLen = 2048;
+constexpr int64_t kShortAll = 8192;
+hipError_t fcg_step(hipStream_t st, FcgState S, int64_t len, double* x, double* r, double* r_old, const double* p,
+                    double* q, double c, const double* t, double tol, int32_t max_iter, int32_t* mirror);
 hipError_t fcg_update_nodecide(hipStream_t st, FcgState S, int64_t len, double* x, double* r, double* r_old,
                                const double* p, const double* q);
 // rho -= alpha t with the stop decision on |rho| (A x = b through the normal equations)
 hipError_t fcg_rho_update(hipStream_t st, FcgState S, int64_t len, double* rho, const double* t, double tol,
                           int32_t max_iter, int32_t* mirror);
-// S.done = src (or 0 when src is null)
-hipError_t fcg_copy_done(hipStream_t st, FcgState S, const int32_t* src);
 // beta = <z, r - r_old> / rz ; rz = <r, z> ; p = z + beta p
-hipError_t fcg_direction(hipStream_t st, FcgState S, int64_t len, const double* r, const double* r_old,
+hipError_t fcg_direction(hipStream_t st, FcgState& S, int64_t len, const double* r, const double* r_old,
                          const double* z, double* p);
 // confirmation on rtrue = b - op(x) for columns with done == 1: done -> 4 if |rtrue| <= tol |b|,
 // else r = rtrue, done -> 0 (restart). relres[j] (device) receives |rtrue| / |b|; mirror <- active
@@ -337,6 +341,8 @@ hipError_t l2_rhs(hipStream_t st, const L2Step& a);
 // publish = false skips the host mirror of the active count for more than 16 columns (the
 // caller publishes with the last step before it reads the mirror)
 hipError_t l2_step(hipStream_t st, const L2Step& a, bool publish = true);
+// the group partials of the last rhs-mode l2_op: *ng blocks [k][s] whose sum is Y^T v
+const double* l2_groups(const L2Step& a, int* ng);
 // out[j][c] = sum of the group partials of the last rhs-mode l2_op (Y^T v), s x k
 hipError_t l2_reduce_to(hipStream_t st, const L2Step& a, double* out, const int32_t* skip);
 
@@ -454,7 +460,8 @@ struct PcgArgs {
   const double* Minv[2];  // preconditioner of each chained solve
   double sigma[2];        // mode 1: operator H + sigma I
   int nsol;               // chained solves (mode 1: 1 or 2; mode 0: 1)
-  const double* rhs;      // [k][s]
+  const double* rhs;      // [k][s], or the sum of nrhs such blocks one after the other
+  int nrhs;               // (0: one)
   double* out;            // [k][s]; zero for columns finished one level up
   const int32_t* parent_done;
   double tol;

@@ -236,8 +236,7 @@ extern "C" msp_status msp_lstsq(void* stream, const msp_precond* P, const double
     MSP_CHECK_HIP(normal_op(st, A, a_t, n, d, lda, w.p, w.q, k, w.S.done, w));
     acc.sweeps += 2;
     acc.sweep_bytes += 2 * abytes;
-    MSP_CHECK_HIP(fcg_alpha_dot(st, w.S, d, w.p, w.q));
-    MSP_CHECK_HIP(fcg_update(st, w.S, d, w.x, w.r, w.ro, w.p, w.q, o.tol, o.max_outer, mirror));
+    MSP_CHECK_HIP(fcg_step(st, w.S, d, w.x, w.r, w.ro, w.p, w.q, 0.0, nullptr, o.tol, o.max_outer, mirror));
     LTRY(prec(w.r, w.z));
     MSP_CHECK_HIP(fcg_direction(st, w.S, d, w.r, w.ro, w.z, w.p));
     ++it;

@@ -110,3 +110,18 @@ def test_zero_columns_and_iteration_caps_in_one_launch():
     X, info = msp.solve(P, A, B, tol=TOL, max_inner=1)  # every inner solve stops at its cap
     assert info["inner_iters"] <= info["outer_iters"] + info["restarts"] + 1
     _check(X, want, b, lam)
+
+
+# level-1 vectors at the limits of the one-block steps: 2048 elements, 8192 over the columns
+@pytest.mark.parametrize("n,k", [(2048, 4), (2048, 5), (2049, 1), (1024, 8), (910, 9), (65, 16), (64, 3)])
+def test_steps_of_short_vectors(n, k):
+    print(f"case short vectors n={n} k={k}", flush=True)
+    s = max(8, min(64, n // 4))
+    P, A, B, b, want, lam = _ridge(n, s, k)
+    X, info = msp.solve(P, A, B, tol=TOL, normal=1)
+    assert info["status"] == "MSP_OK", info
+    _check(X, want, b, lam)
+    P, A, B, b, want, lam = _psd(n, s, k)
+    X, info = msp.solve(P, A, B, tol=TOL)
+    assert info["status"] == "MSP_OK", info
+    _check(X, want, b, lam)
