@@ -79,10 +79,15 @@ __global__ void k_bucket_colscan(int32_t* __restrict__ H, int nchunks, int nrows
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= nrows) return;
   int32_t run = 0;
-  for (int c = 0; c < nchunks; ++c) {
-    const int32_t t = H[(int64_t)c * nrows + j];
-    H[(int64_t)c * nrows + j] = run;
-    run += t;
+  for (int c0 = 0; c0 < nchunks; c0 += 16) {  // sixteen chunks' counts in flight
+    int32_t t[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t[u] = c0 + u < nchunks ? H[(int64_t)(c0 + u) * nrows + j] : 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (c0 + u < nchunks) H[(int64_t)(c0 + u) * nrows + j] = run;
+      run += t[u];
+    }
   }
   total[j] = run;
 }
@@ -424,6 +429,8 @@ hipError_t tiles_dispatch(hipStream_t st, const TA* A, int64_t m, int64_t n, int
 }
 
 // ---- out[j, :] = scale * sum_{e in bucket j} sign(e) X[col(e), :] -----------------
+// Reads gamma rows of X per row of X, from the caches mostly: 512 x 512 from n = 32768, gamma =
+// 8 and 2048 x 512 from the same took 455 us one row after the other, 260 us with eight in flight.
 template <class TX>
 __global__ void __launch_bounds__(256) k_gather_rows(const TX* __restrict__ X, int64_t ldx, int64_t ncols,
                                                      const int32_t* __restrict__ offsets,
@@ -433,7 +440,18 @@ __global__ void __launch_bounds__(256) k_gather_rows(const TX* __restrict__ X, i
   const int p0 = offsets[j], p1 = offsets[j + 1];
   for (int64_t c = threadIdx.x; c < ncols; c += blockDim.x) {
     double acc = 0.0;
-    for (int p = p0; p < p1; ++p) {
+    int p = p0;
+    for (; p + 8 <= p1; p += 8) {  // eight rows' loads in flight, added in entry order
+      int32_t ent[8];
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ent[u] = entries[p + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = (double)X[(int64_t)(ent[u] >> 1) * ldx + c];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += (ent[u] & 1) ? -v[u] : v[u];
+    }
+    for (; p < p1; ++p) {
       const int32_t ent = entries[p];
       const double v = (double)X[(int64_t)(ent >> 1) * ldx + c];
       acc += (ent & 1) ? -v : v;

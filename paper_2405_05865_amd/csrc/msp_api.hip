@@ -100,6 +100,7 @@ SketchWs carve_sketch(WsCarver& w, int64_t n, int64_t s, int32_t gamma) {
 struct NysWs {
   double *Wm, *G, *Minv, *Minv2, *tmp, *small, *gpart, *scal;
   double *est_w, *est_c, *est_part;  // PSD: the lam0 estimator's W^{-1}, C^T C, Gram partials
+  double* est_diag;                  // and its trace partials
   int32_t* status;
   int32_t* phi_rows;
   int8_t* phi_signs;
@@ -119,6 +120,7 @@ NysWs carve_nystrom(WsCarver& w, msp_structure st, int64_t m, int64_t n, int64_t
     o.est_w = w.take<double>(s * s);
     o.est_c = w.take<double>(s * s);
     o.est_part = w.take<double>((size_t)gram_splits(n, s) * s * s + 1);
+    o.est_diag = w.take<double>(lambda0_part_doubles(s));
   } else {
     o.Wm = nullptr;
     o.Minv2 = w.take<double>(s * s);
@@ -245,8 +247,7 @@ msp_status estimate_lambda0(hipStream_t st, msp_precond* H, const NysWs& o, cons
     MSP_CHECK_HIP(launch_gram(st, (const double*)H->Y, n, s, H->ldy, o.est_c, o.est_part, sp));
   else
     MSP_CHECK_HIP(launch_gram_f32(st, (const float*)H->Y, n, s, H->ldy, o.est_c, o.est_part, sp));
-  MSP_CHECK_HIP(launch_diag_sum(st, A, a_t, n, lda, o.scal));
-  MSP_CHECK_HIP(launch_lambda0_est(st, o.est_w, o.est_c, s, 0.5 * (double)s, o.scal));
+  MSP_CHECK_HIP(launch_lambda0_est(st, o.est_w, o.est_c, s, A, a_t, n, lda, 0.5 * (double)s, o.scal, o.est_diag));
   double v[3] = {0, 0, 0};
   int32_t bad = 0;
   MSP_CHECK_HIP(hipMemcpyAsync(v, o.scal, sizeof v, hipMemcpyDeviceToHost, st));

@@ -90,12 +90,12 @@ hipError_t launch_combine_sym(hipStream_t st, int64_t s, double a, const double*
 hipError_t launch_symmetrize(hipStream_t st, int64_t s, double* Wm);
 // trace(M) -> *out (device scalar)
 hipError_t launch_trace(hipStream_t st, int64_t s, const double* M, double* out);
-// *out = sum_i A[i, i] in FP64 for an F64, F32 or BF16 matrix (device scalar)
-hipError_t launch_diag_sum(hipStream_t st, const void* A, msp_dtype t, int64_t n, int64_t lda, double* out);
-// lam0 estimate from the trace deficit of the Nystrom approximation: with scal[0] = tr A,
-// scal[1] <- <Winv, C^T C>_F = tr(Winv C^T C) and scal[2] <- (2/l) max(scal[0] - scal[1], 0)
-hipError_t launch_lambda0_est(hipStream_t st, const double* Winv, const double* CtC, int64_t s, double l,
-                              double* scal);
+// lam0 estimate from the trace deficit of the Nystrom approximation: scal[0] <- tr A (A n x n,
+// F64, F32 or BF16), scal[1] <- <Winv, C^T C>_F = tr(Winv C^T C) and scal[2] <- (2/l) max(scal[0]
+// - scal[1], 0); part: lambda0_part_doubles(s) doubles of scratch
+size_t lambda0_part_doubles(int64_t s);
+hipError_t launch_lambda0_est(hipStream_t st, const double* Winv, const double* CtC, int64_t s, const void* A,
+                              msp_dtype t, int64_t n, int64_t lda, double l, double* scal, double* part);
 // In-place inverse of SPD M (s x s) by Gauss-Jordan sweeps, shifted by
 // mu = shift_rel * trace / s; tmp: s*s doubles; status: device int (0 ok, 1 not PD).
 // Result lands in M.
