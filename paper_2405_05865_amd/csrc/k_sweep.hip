@@ -8,6 +8,7 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -27,35 +28,46 @@ typedef double nd2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef float nf4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t nu4 __attribute__((ext_vector_type(4), aligned(2)));
 
+// a 16-byte load, through the caches (NTL = false) or past them
+template <bool NTL, class V>
+__device__ __forceinline__ V load16(const V* p) {
+  if constexpr (NTL) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 // VEC elements of A per 16-byte load, converted to TC
 template <class TA, class TC, int VEC>
 struct Vec16;
 template <>
 struct Vec16<double, double, 2> {
+  template <bool NTL>
   static __device__ __forceinline__ void load(const double* p, double* o) {
-    const nd2 v = __builtin_nontemporal_load(reinterpret_cast<const nd2*>(p));
+    const nd2 v = load16<NTL>(reinterpret_cast<const nd2*>(p));
     o[0] = v.x;
     o[1] = v.y;
   }
 };
 template <>
 struct Vec16<float, float, 4> {
+  template <bool NTL>
   static __device__ __forceinline__ void load(const float* p, float* o) {
-    const nf4 v = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(p));
+    const nf4 v = load16<NTL>(reinterpret_cast<const nf4*>(p));
     o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
   }
 };
 template <>
 struct Vec16<float, double, 4> {
+  template <bool NTL>
   static __device__ __forceinline__ void load(const float* p, double* o) {
-    const nf4 v = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(p));
+    const nf4 v = load16<NTL>(reinterpret_cast<const nf4*>(p));
     o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
   }
 };
 template <>
 struct Vec16<__hip_bfloat16, float, 8> {
+  template <bool NTL>
   static __device__ __forceinline__ void load(const __hip_bfloat16* p, float* o) {
-    const nu4 v = __builtin_nontemporal_load(reinterpret_cast<const nu4*>(p));
+    const nu4 v = load16<NTL>(reinterpret_cast<const nu4*>(p));
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -80,7 +92,7 @@ __device__ __forceinline__ float scalar_as<__hip_bfloat16, float>(const __hip_bf
 
 // Block of NT threads computes R rows of Y = A X (+ lam X) for K vectors; each thread
 // keeps UNR 16-byte loads per row in flight.
-template <class TA, class TC, int VEC, int R, int K, int UNR>
+template <class TA, class TC, int VEC, int R, int K, int UNR, bool NTL>
 __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t lda, int64_t rows, int64_t cols,
                                             const double* __restrict__ X, int64_t ldx, double* __restrict__ Y,
                                             int64_t ldy, int k, int j0, double lam, int diag,
@@ -107,7 +119,7 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
 #pragma unroll
-      for (int r = 0; r < R; ++r) Vec16<TA, TC, VEC>::load(arow[r] + c + u * STEP, a[u][r]);
+      for (int r = 0; r < R; ++r) Vec16<TA, TC, VEC>::template load<NTL>(arow[r] + c + u * STEP, a[u][r]);
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       TC xv[K][VEC];
@@ -136,7 +148,7 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       TC a[VEC];
-      Vec16<TA, TC, VEC>::load(arow[r] + c, a);
+      Vec16<TA, TC, VEC>::template load<NTL>(arow[r] + c, a);
 #pragma unroll
       for (int j = 0; j < K; ++j)
 #pragma unroll
@@ -190,7 +202,7 @@ __global__ void __launch_bounds__(NT) k_gemv(const TA* __restrict__ A, int64_t l
 // Y[:, j] = A^T X[:, j]: block (column tile, row tile); partial over the row tile, or with one
 // row tile the result itself (direct). Eight rows' loads are in flight per thread: the short
 // products of the inner levels (s rows) are one or a few such rounds.
-template <class TA, class TC, int VEC, int K>
+template <class TA, class TC, int VEC, int K, bool NTL>
 __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t lda, int64_t rows, int64_t cols,
                                               const double* __restrict__ X, int64_t ldx, int k, int j0,
                                               int64_t rows_per_tile, double* __restrict__ out, int64_t ldo,
@@ -218,7 +230,7 @@ __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t
     for (; r + U <= re; r += U) {
       TC a[U][VEC];
 #pragma unroll
-      for (int u = 0; u < U; ++u) Vec16<TA, TC, VEC>::load(A + (r + u) * lda + c, a[u]);
+      for (int u = 0; u < U; ++u) Vec16<TA, TC, VEC>::template load<NTL>(A + (r + u) * lda + c, a[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u) add(r + u, a[u]);
     }
@@ -226,7 +238,7 @@ __global__ void __launch_bounds__(NT) k_gemv_t(const TA* __restrict__ A, int64_t
   for (; r < re; ++r) {
     TC a[VEC];
     if (full) {
-      Vec16<TA, TC, VEC>::load(A + r * lda + c, a);
+      Vec16<TA, TC, VEC>::template load<NTL>(A + r * lda + c, a);
     } else {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) a[v] = (c + v < cols) ? scalar_as<TA, TC>(A + r * lda + c + v) : (TC)0;
@@ -263,14 +275,25 @@ __global__ void k_sum_tiles(const double* __restrict__ part, int tiles, int64_t 
   Y[(int64_t)j * ldy + c] = acc;
 }
 
+// matrices that the memory-side cache holds between sweeps are loaded through the caches,
+// larger ones past them. us per sweep, cached / streamed, FP64: n = 2048 4.9 / 6.9, 6000 43 / 45,
+// 8192 93 / 82, 32768 1425 / 1245.
+bool past_caches(int64_t rows, int64_t cols, int64_t es) { return rows * cols * es > (int64_t(384) << 20); }
+
 template <class TA, class TC, int VEC, int R, int K, int UNR = 1>
 hipError_t gemv_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X,
                   int64_t ldx, double* Y, int64_t ldy, int k, double lam, bool diag, const int32_t* skip,
                   double* dot_part, int* nblocks) {
   const int64_t blocks = (rows + R - 1) / R;
-  for (int j0 = 0; j0 < k; j0 += K)
-    hipLaunchKernelGGL((k_gemv<TA, TC, VEC, R, K, UNR>), dim3((unsigned)blocks), dim3(NT), 0, st, A, lda, rows, cols, X,
-                       ldx, Y, ldy, k, j0, lam, diag ? 1 : 0, skip, dot_part, k);
+  const bool ntl = past_caches(rows, cols, sizeof(TA));
+  for (int j0 = 0; j0 < k; j0 += K) {
+    if (ntl)
+      hipLaunchKernelGGL((k_gemv<TA, TC, VEC, R, K, UNR, true>), dim3((unsigned)blocks), dim3(NT), 0, st, A, lda, rows,
+                         cols, X, ldx, Y, ldy, k, j0, lam, diag ? 1 : 0, skip, dot_part, k);
+    else
+      hipLaunchKernelGGL((k_gemv<TA, TC, VEC, R, K, UNR, false>), dim3((unsigned)blocks), dim3(NT), 0, st, A, lda, rows,
+                         cols, X, ldx, Y, ldy, k, j0, lam, diag ? 1 : 0, skip, dot_part, k);
+  }
   if (nblocks) *nblocks = (int)blocks;
   return hipGetLastError();
 }
@@ -280,7 +303,11 @@ hipError_t gemv_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
                   int64_t ldx, double* Y, int64_t ldy, int k, double lam, bool diag, const int32_t* skip,
                   double* dot_part, int* nblocks) {
   if (k == 1) return gemv_t<TA, TC, VEC, 4, 1, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
-  if (k == 2) return gemv_t<TA, TC, VEC, 8, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
+  // rows per block and loads in flight, us per FP64 sweep: two columns, 4 rows x 2 loads 45 (n =
+  // 6000) and 6.2 (n = 2048), 8 x 1 63 and 12.5; four columns, 8 x 2 52 and 206 (n = 6000, 12000), 4
+  // x 1 63 and 225, but 10.9 against 7.4 at n = 1024 and 35 against 29 at n = 4096 (too few blocks)
+  if (k == 2) return gemv_t<TA, TC, VEC, 4, 2, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
+  if (k <= 4 && rows >= 5000 && sizeof(TA) == 8) return gemv_t<TA, TC, VEC, 8, 4, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
   if (k <= 4) return gemv_t<TA, TC, VEC, 4, 4>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
   return gemv_t<TA, TC, VEC, 4, 8>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
 }
@@ -299,14 +326,19 @@ hipError_t gemvT_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int6
   double* out = direct ? Y : part;
   const int64_t ldo = direct ? ldy : cols;
   const dim3 grid((unsigned)ctiles, (unsigned)rtiles);
-  if (k == 1) {
-    hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, 1>), grid, dim3(NT), 0, st, A, lda, rows, cols, X, ldx, k, 0, rpt, out, ldo,
-                       skip, direct);
-  } else {
-    for (int j0 = 0; j0 < k; j0 += 4)
-      hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, 4>), grid, dim3(NT), 0, st, A, lda, rows, cols, X, ldx, k, j0, rpt, out,
-                         ldo, skip, direct);
-  }
+  const bool ntl = past_caches(rows, cols, sizeof(TA));
+  auto go = [&](auto kc, int j0) {
+    constexpr int K = decltype(kc)::value;
+    if (ntl)
+      hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, K, true>), grid, dim3(NT), 0, st, A, lda, rows, cols, X, ldx, k, j0, rpt,
+                         out, ldo, skip, direct);
+    else
+      hipLaunchKernelGGL((k_gemv_t<TA, TC, VEC, K, false>), grid, dim3(NT), 0, st, A, lda, rows, cols, X, ldx, k, j0, rpt,
+                         out, ldo, skip, direct);
+  };
+  if (k == 1) go(std::integral_constant<int, 1>{}, 0);
+  else
+    for (int j0 = 0; j0 < k; j0 += 4) go(std::integral_constant<int, 4>{}, j0);
   if (!direct) {
     const int64_t len = cols * k;
     hipLaunchKernelGGL(k_sum_tiles, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, part, (int)rtiles, cols, k,

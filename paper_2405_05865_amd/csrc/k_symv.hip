@@ -4,24 +4,28 @@
 // triangle is used twice from one load: in the row dot (A p)_i and, mirrored, in the
 // column sum (A^T p)_j.
 //
-// The lower triangle is cut into 256 x 256 tiles (I, J), J <= I, one per block, numbered
+// The lower triangle is cut into T x T tiles (I, J), J <= I, one per block (T = 64, 128 or 256,
+// symv_tile), numbered
 // b = I (I + 1) / 2 + J. A block has four wavefronts; wavefront w takes the tile rows
-// w + 4 (g + 4 t) (lane group g = lane / 16) and all 256 columns: 16 lanes share a row
+// w + 4 (g + 4 t) (lane group g = lane / 16) and all T columns: 16 lanes share a row
 // (16-byte chunks, 256 contiguous bytes per row and load), so the row dots reduce over 16
-// lanes and the column sums over the 4 lane groups and then the 4 wavefronts (LDS). A
+// lanes (register moves, no LDS) and the column sums over the 4 lane groups and then the 4
+// wavefronts (LDS). A
 // tile writes its row partials (ypart) and column partials (zpart); a second kernel adds,
 // for each row, the row partials of its tile row and the column partials of its tile
 // column in a fixed order, applies the shift and writes the <p, q> partials of the
 // level-1 update. Diagonal tiles mask the strict upper triangle (not loaded) and the
 // diagonal from the column sums.
 #include "msp_internal.h"
+#include "wave_ops.h"
 
 #include <hip/hip_bf16.h>
+
+#include <algorithm>
 
 namespace {
 
 constexpr int WAVE = 64;
-constexpr int T = 256;          // tile edge
 constexpr int NWV = 4;          // wavefronts per block (rows interleaved)
 constexpr int LC = 16;          // lanes along a row
 constexpr int LR = WAVE / LC;   // lane groups along a column
@@ -33,13 +37,21 @@ typedef double sd2 __attribute__((ext_vector_type(2)));
 typedef float sf4 __attribute__((ext_vector_type(4)));
 typedef uint32_t su4 __attribute__((ext_vector_type(4)));
 
+// a 16-byte load, through the caches (NTL = false) or past them
+template <bool NTL, class V>
+__device__ __forceinline__ V load16(const V* p) {
+  if constexpr (NTL) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 template <class TA, class TC>
 struct Chunk;  // one 16-byte chunk of a row as VEC values of the arithmetic type
 template <>
 struct Chunk<double, double> {
   static constexpr int VEC = 2;
+  template <bool NTL>
   static __device__ __forceinline__ void load(const double* p, double* o) {
-    const sd2 v = __builtin_nontemporal_load(reinterpret_cast<const sd2*>(p));
+    const sd2 v = load16<NTL>(reinterpret_cast<const sd2*>(p));
     o[0] = v.x;
     o[1] = v.y;
   }
@@ -48,8 +60,9 @@ struct Chunk<double, double> {
 template <>
 struct Chunk<float, float> {
   static constexpr int VEC = 4;
+  template <bool NTL>
   static __device__ __forceinline__ void load(const float* p, float* o) {
-    const sf4 v = __builtin_nontemporal_load(reinterpret_cast<const sf4*>(p));
+    const sf4 v = load16<NTL>(reinterpret_cast<const sf4*>(p));
     o[0] = v.x;
     o[1] = v.y;
     o[2] = v.z;
@@ -60,8 +73,9 @@ struct Chunk<float, float> {
 template <>
 struct Chunk<__hip_bfloat16, float> {
   static constexpr int VEC = 8;
+  template <bool NTL>
   static __device__ __forceinline__ void load(const __hip_bfloat16* p, float* o) {
-    const su4 v = __builtin_nontemporal_load(reinterpret_cast<const su4*>(p));
+    const su4 v = load16<NTL>(reinterpret_cast<const su4*>(p));
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -71,11 +85,6 @@ struct Chunk<__hip_bfloat16, float> {
   }
   static __device__ __forceinline__ float one(const __hip_bfloat16* p) { return __bfloat162float(*p); }
 };
-
-template <class TC>
-__device__ __forceinline__ TC xor_sum(TC v, int mask) {
-  return v + __shfl_xor(v, mask, WAVE);
-}
 
 __device__ __forceinline__ int tile_row(int b) {
   int I = (int)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
@@ -87,7 +96,7 @@ __device__ __forceinline__ int tile_row(int b) {
 // the rows of one tile that belong to this wavefront. MASK: diagonal tile or a tile
 // reaching past n (per-element checks); otherwise every chunk is whole and below the
 // diagonal.
-template <class TA, class TC, bool MASK>
+template <class TA, class TC, int T, bool NTL, bool MASK>
 __device__ __forceinline__ void tile_rows(const TA* __restrict__ A, int64_t lda, int64_t n,
                                           const double* __restrict__ x, int64_t r0, int64_t c0, bool diag,
                                           TC (&xj)[T / (LC * Chunk<TA, TC>::VEC)][Chunk<TA, TC>::VEC],
@@ -95,9 +104,10 @@ __device__ __forceinline__ void tile_rows(const TA* __restrict__ A, int64_t lda,
                                           double* ys) {
   constexpr int VEC = Chunk<TA, TC>::VEC;
   constexpr int M = T / (LC * VEC);
+  constexpr int UNR = T == 256 ? 2 : 4;
   const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
   const int kap = lane % LC, rho = lane / LC;
-#pragma unroll 2
+#pragma unroll UNR
   for (int t = 0; t < T / (LR * NWV); ++t) {
     const int rl = w + NWV * (rho + LR * t);
     const int64_t gi = r0 + rl;
@@ -110,9 +120,9 @@ __device__ __forceinline__ void tile_rows(const TA* __restrict__ A, int64_t lda,
       for (int m = 0; m < M; ++m) {
         const int64_t col = c0 + m * (LC * VEC) + kap * VEC;
         if (!MASK) {
-          Chunk<TA, TC>::load(arow + col, a[m]);
+          Chunk<TA, TC>::template load<NTL>(arow + col, a[m]);
         } else if (col + VEC <= n && (!diag || col + VEC - 1 <= gi)) {
-          Chunk<TA, TC>::load(arow + col, a[m]);
+          Chunk<TA, TC>::template load<NTL>(arow + col, a[m]);
         } else {
 #pragma unroll
           for (int v = 0; v < VEC; ++v) {
@@ -134,13 +144,12 @@ __device__ __forceinline__ void tile_rows(const TA* __restrict__ A, int64_t lda,
           }
         }
     }
-#pragma unroll
-    for (int o = 1; o < LC; o <<= 1) ysum = xor_sum(ysum, o);
+    ysum = wave_ops::row_sum(ysum);  // the 16 lanes of the row
     if (kap == 0) ys[rl] = (double)ysum;
   }
 }
 
-template <class TA, class TC>
+template <class TA, class TC, int T, bool NTL>
 __global__ void __launch_bounds__(NB) k_symv_tiles(const TA* __restrict__ A, int64_t lda, int64_t n,
                                                   const double* __restrict__ x, const int32_t* __restrict__ skip,
                                                   double* __restrict__ ypart, double* __restrict__ zpart) {
@@ -167,17 +176,17 @@ __global__ void __launch_bounds__(NB) k_symv_tiles(const TA* __restrict__ A, int
   const bool diag = I == J;
   const bool edge = r0 + T > n;  // the last tile row (and with it the last tile column)
   if (diag || edge)
-    tile_rows<TA, TC, true>(A, lda, n, x, r0, c0, diag, xj, za, ys);
+    tile_rows<TA, TC, T, NTL, true>(A, lda, n, x, r0, c0, diag, xj, za, ys);
   else
-    tile_rows<TA, TC, false>(A, lda, n, x, r0, c0, diag, xj, za, ys);
+    tile_rows<TA, TC, T, NTL, false>(A, lda, n, x, r0, c0, diag, xj, za, ys);
   // column sums over the 4 lane groups, then over the wavefronts in a fixed order
 #pragma unroll
   for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
       TC s = za[m][v];
-      s = xor_sum(s, 16);
-      s = xor_sum(s, 32);
+      s = wave_ops::swap16_add(s, s);
+      s = wave_ops::swap32_add(s, s);
       if (rho == 0) zs[w][m * (LC * VEC) + kap * VEC + v] = (double)s;
     }
   __syncthreads();
@@ -193,6 +202,7 @@ __global__ void __launch_bounds__(NB) k_symv_tiles(const TA* __restrict__ A, int
 // column) and the 16 sums combine in a fixed order. Measured against 256 x 512 tiles with
 // eight wavefronts on the same GPU, these tiles stream about 3% faster (699 against 720 us
 // per n = 32768 sweep), and 16 wavefronts per row list cut the reduction from 14 to 6 us.
+template <int T>
 __global__ void __launch_bounds__(NG * NR) k_symv_reduce(const double* __restrict__ ypart,
                                                        const double* __restrict__ zpart, int64_t n, int N,
                                                        const double* __restrict__ x, double lam, int diag,
@@ -232,27 +242,55 @@ __global__ void __launch_bounds__(NG * NR) k_symv_reduce(const double* __restric
   }
 }
 
-template <class TA, class TC>
+template <class TA, class TC, int T, bool NTL>
 hipError_t symv_t(hipStream_t st, const TA* A, int64_t n, int64_t lda, const double* x, double* y, double lam,
                   bool diag, const int32_t* skip, double* part, double* dot_part, int* nblocks) {
   const int N = (int)((n + T - 1) / T);
   const int64_t tiles = (int64_t)N * (N + 1) / 2;
   double* ypart = part;
   double* zpart = part + tiles * T;
-  hipLaunchKernelGGL((k_symv_tiles<TA, TC>), dim3((unsigned)tiles), dim3(NB), 0, st, A, lda, n, x, skip, ypart,
+  hipLaunchKernelGGL((k_symv_tiles<TA, TC, T, NTL>), dim3((unsigned)tiles), dim3(NB), 0, st, A, lda, n, x, skip, ypart,
                      zpart);
   const unsigned rb = (unsigned)((n + NR - 1) / NR);
-  hipLaunchKernelGGL(k_symv_reduce, dim3(rb), dim3(NG * NR), 0, st, ypart, zpart, n, N, x, lam, diag ? 1 : 0, skip, y,
+  hipLaunchKernelGGL(k_symv_reduce<T>, dim3(rb), dim3(NG * NR), 0, st, ypart, zpart, n, N, x, lam, diag ? 1 : 0, skip, y,
                      dot_part);
   if (nblocks) *nblocks = (int)rb;
   return hipGetLastError();
 }
 
+// The tile edge by the bytes of the lower triangle. Small matrices are bound by latency (10
+// blocks of 256 x 256 at n = 1024, each a chain of sixteen row rounds): smaller tiles, whose
+// extra partials stay in the caches. us per sweep with edge 256 / 128 / 64: FP64 n = 1024 20.6 /
+// 10.2 / 6.7, 4096 28 / 19 / 16, 8192 56 / 48 / 47, 16384 189 / 185 / 200; F32 n = 12000 65 / 59 /
+// 68, 32768 387 / 440 / 504. Up to about the size of the memory-side cache the loads go through
+// the caches (n = 8192 with edge 128: 48 us, 50 us past them; n = 16384: 202 us, 185 us).
+// (Before, with edge 256 and the row sums exchanged through LDS: 22.9 us at n = 1024, 70 us for
+// F32 n = 12000.) A BF16 row chunk needs an edge of 128.
+constexpr int64_t kTile64Bytes = int64_t(80) << 20, kTile128Bytes = int64_t(400) << 20;
+int symv_tile(int64_t n, int64_t es) {
+  const int64_t bytes = n * n / 2 * es;
+  return bytes <= kTile64Bytes && es > 2 ? 64 : (bytes <= kTile128Bytes ? 128 : 256);
+}
+
+template <class TA, class TC>
+hipError_t symv_d(hipStream_t st, const TA* A, int64_t n, int64_t lda, const double* x, double* y, double lam,
+                  bool diag, const int32_t* skip, double* part, double* dot_part, int* nblocks) {
+  const int T = symv_tile(n, sizeof(TA));
+  if constexpr (sizeof(TA) > 2)
+    if (T == 64) return symv_t<TA, TC, 64, false>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
+  if (T == 128) return symv_t<TA, TC, 128, false>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
+  return symv_t<TA, TC, 256, true>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
+}
+
 }  // namespace
 
 size_t symv_part_doubles(int64_t n) {
-  const int64_t N = (n + T - 1) / T;
-  return (size_t)(N * (N + 1)) * T + 64;  // row and column partials of every tile
+  size_t most = 0;  // row and column partials of every tile, for whichever storage type
+  for (int64_t es : {2, 4, 8}) {
+    const int64_t T = symv_tile(n, es), N = (n + T - 1) / T;
+    most = std::max(most, (size_t)(N * (N + 1)) * T + 64);
+  }
+  return most;
 }
 
 bool symv_supported(const void* A, msp_dtype t, int64_t lda, int64_t k) {
@@ -267,12 +305,12 @@ hipError_t launch_symv(hipStream_t st, const void* A, msp_dtype a_t, int64_t n, 
   if (n < 1 || !symv_supported(A, a_t, lda, 1)) return hipErrorInvalidValue;
   switch (a_t) {
     case MSP_F64:
-      return symv_t<double, double>(st, (const double*)A, n, lda, x, y, lam, diag_shift, skip, part, dot_part,
+      return symv_d<double, double>(st, (const double*)A, n, lda, x, y, lam, diag_shift, skip, part, dot_part,
                                     nblocks);
     case MSP_F32:
-      return symv_t<float, float>(st, (const float*)A, n, lda, x, y, lam, diag_shift, skip, part, dot_part, nblocks);
+      return symv_d<float, float>(st, (const float*)A, n, lda, x, y, lam, diag_shift, skip, part, dot_part, nblocks);
     case MSP_BF16:
-      return symv_t<__hip_bfloat16, float>(st, (const __hip_bfloat16*)A, n, lda, x, y, lam, diag_shift, skip, part,
+      return symv_d<__hip_bfloat16, float>(st, (const __hip_bfloat16*)A, n, lda, x, y, lam, diag_shift, skip, part,
                                            dot_part, nblocks);
   }
   return hipErrorInvalidValue;

@@ -21,6 +21,21 @@ __device__ __forceinline__ double row_move(double v) {
   return __hiloint2double(hi, lo);
 }
 
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// sum over the 16 lanes of a row, valid in all of them
+template <class T>
+__device__ __forceinline__ T row_sum(T v) {
+  v += row_move<kXor1>(v);
+  v += row_move<kXor2>(v);
+  v += row_move<kHalfMirror>(v);
+  v += row_move<kRor8>(v);
+  return v;
+}
+
 // a and b with the odd 16-lane rows of a exchanged for the even rows of b: the sum of the
 // two results is a's pairs of rows in the even rows and b's in the odd ones
 __device__ __forceinline__ double swap16_add(double a, double b) {
@@ -35,12 +50,18 @@ __device__ __forceinline__ double swap32_add(double a, double b) {
   return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
 
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+}
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+}
+
 // sum over the 64 lanes, valid in every lane
 __device__ __forceinline__ double wave_sum(double v) {
-  v += row_move<kXor1>(v);
-  v += row_move<kXor2>(v);
-  v += row_move<kHalfMirror>(v);
-  v += row_move<kRor8>(v);
+  v = row_sum(v);
   v = swap16_add(v, v);
   return swap32_add(v, v);
 }
