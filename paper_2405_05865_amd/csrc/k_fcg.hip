@@ -78,6 +78,8 @@ __device__ __forceinline__ void count_active(FcgState S, int32_t* mirror) {
       // reads them only after synchronising the stream, which orders them (no fence here)
       __hip_atomic_store(mirror, cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       __hip_atomic_store(mirror + 1, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store((uint64_t*)(mirror + 2), decision_word(S.seq, cnt, mx), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
 }

@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -680,6 +681,35 @@ msp_status sync(SolveCtx& c) {
   return *slot(c, SLOT_FAIL) ? kPcgGaveUp : MSP_OK;
 }
 
+// Waits for the decision that the last deciding kernel of level L publishes to its slot, by
+// polling the mapped mirror: the kernels queued behind the decision keep the GPU busy while
+// the host enqueues the next step (a stream synchronisation waits for them too and left the
+// GPU idle for the host's round trip, 10 to 25 us of every step). Returns the active count.
+msp_status wait_decision(SolveCtx& c, const Level& L, int slotid, int* active, int* iters = nullptr) {
+  const uint64_t want = L.S.seq & ((1u << kSeqBits) - 1);
+  const uint64_t* word = (const uint64_t*)(c.hf + slotid + 2);
+  uint64_t w = 0;
+  for (uint32_t spin = 1;; ++spin) {
+    w = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+    if (*slot(c, SLOT_FAIL)) return kPcgGaveUp;
+    if (w >> 44 == want) break;
+    if (spin % 1024 == 0) {  // an error, or an idle stream without the decision, ends the wait
+      const hipError_t e = hipStreamQuery(c.st);
+      if (e == hipSuccess) {
+        w = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+        if (w >> 44 == want) break;
+        return msp_fail(MSP_ERR_HIP, "a level's decision did not reach the host");
+      }
+      if (e != hipErrorNotReady) MSP_CHECK_HIP(e);
+      std::this_thread::yield();
+    }
+    __builtin_ia32_pause();
+  }
+  *active = (int)((w >> 32) & 0xFFF);
+  if (iters) *iters = (int)(uint32_t)w;
+  return MSP_OK;
+}
+
 // profiled sweeps: an event pair around each level-1 sweep launch
 msp_status ev_begin(SolveCtx& c, hipEvent_t* stop_out) {
   *stop_out = nullptr;
@@ -1103,7 +1133,6 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
     MSP_CHECK_HIP(launch_small_mv(c.st, s, c.H2, c.rhs2, k, pdone, c.L2.x));
     MSP_CHECK_HIP(
         launch_y_z(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, k, 1.0 / P->lt, r, n, -1.0 / P->lt, pdone, z, n));
-    TRY(sync(c));  // the level-1 mirror is read by the caller after SolveM1
     return MSP_OK;
   }
   if (c.use_p) {  // the whole solve in one launch, H applied through G2 = H M2^{-1}
@@ -1157,19 +1186,20 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
 msp_status psd_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int max_outer) {
   Level& L = c.L1;
   const int64_t n = c.n, k = c.k;
+  ++L.S.seq;
   MSP_CHECK_HIP(fcg_init(c.st, L.S, n, B, ldb, L.r, L.x, nullptr, c.df + SLOT_L1));
   TRY(psd_solve_m1(c, L.r, L.z));
   MSP_CHECK_HIP(fcg_first_dir(c.st, L.S, n, L.r, L.z, L.p));
-  int it = 0;
+  int it = 0, active = 0, iters = 0;
   while (true) {
-    // the level-1 mirror is current where psd_solve_m1 synchronised after the update
-    if (c.use_p) TRY(sync(c));
-    if (*slot(c, SLOT_L1) == 0) {
+    TRY(wait_decision(c, L, SLOT_L1, &active, &iters));
+    if (active == 0) {
       TRY(sweep(c, c.A_cf, c.cf_t, n, n, L.x, n, L.q, n, true, nullptr, false, true, false));
       MSP_CHECK_HIP(launch_axpby(c.st, n, k, 1.0, B, ldb, -1.0, L.q, n, L.q, n, nullptr));
+      ++L.S.seq;
       MSP_CHECK_HIP(fcg_confirm(c.st, L.S, n, L.q, L.r, tol, c.relres, c.df + SLOT_L1));
-      TRY(sync(c));
-      if (*slot(c, SLOT_L1) == 0) break;
+      TRY(wait_decision(c, L, SLOT_L1, &active, &iters));
+      if (active == 0) break;
       c.acc.restarts += 1;
       TRY(psd_solve_m1(c, L.r, L.z));
       MSP_CHECK_HIP(fcg_first_dir(c.st, L.S, n, L.r, L.z, L.p));
@@ -1177,13 +1207,14 @@ msp_status psd_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
     }
     if (it >= max_outer) break;
     TRY(sweep(c, c.A_sw, c.sw_t, n, n, L.p, n, L.q, n, true, L.S.done, true, false, true));
+    ++L.S.seq;
     MSP_CHECK_HIP(fcg_update(c.st, L.S, n, L.x, L.r, L.ro, L.p, L.q, tol, max_outer, c.df + SLOT_L1, c.gpart,
                              c.nb_last));
     TRY(psd_solve_m1(c, L.r, L.z));
     MSP_CHECK_HIP(fcg_direction(c.st, L.S, n, L.r, L.ro, L.z, L.p));
     ++it;
   }
-  c.acc.outer_iters += (int32_t)*slot(c, SLOT_L1 + 1);
+  c.acc.outer_iters += iters;
   return MSP_OK;
 }
 
@@ -1295,22 +1326,24 @@ msp_status gen_solve_m1(SolveCtx& c, const double* r, double* z) {
     MSP_CHECK_HIP(launch_axpby(c.st, n, k, 1.0 / P->lt, r, n, -1.0 / P->lt, c.nvec, n, z, n, pdone));
     return MSP_OK;
   }
+  ++L.S.seq;
   MSP_CHECK_HIP(fcg_init(c.st, L.S, s, c.rhs2, s, L.r, L.x, pdone, c.df + SLOT_L2));
   TRY(gen_solve_m2(c, L.r, L.z, L.S.done));
   MSP_CHECK_HIP(fcg_first_dir(c.st, L.S, s, L.r, L.z, L.p));
-  for (int it = 0; it < c.o->max_inner; ++it) {
-    TRY(sync(c));
-    if (*slot(c, SLOT_L2) == 0) break;
+  int active = 0, iters = 0;
+  for (int it = 0;; ++it) {
+    TRY(wait_decision(c, L, SLOT_L2, &active, &iters));
+    if (active == 0 || it >= c.o->max_inner) break;
     double cq = 0.0;
     const double* tq = nullptr;
     TRY(gen_op2(c, L.p, L.q, L.S.done, &cq, &tq));
+    ++L.S.seq;
     MSP_CHECK_HIP(fcg_step(c.st, L.S, s, L.x, L.r, L.ro, L.p, L.q, cq, tq, c.o->inner_tol, c.o->max_inner,
                            c.df + SLOT_L2));
     TRY(gen_solve_m2(c, L.r, L.z, L.S.done));
     MSP_CHECK_HIP(fcg_direction(c.st, L.S, s, L.r, L.ro, L.z, L.p));
   }
-  TRY(sync(c));
-  c.acc.inner_iters += *slot(c, SLOT_L2 + 1);
+  c.acc.inner_iters += iters;
   // w^ = (r - A^T (A~ y^)) / lam~
   if (c.form == 1) {  // A^T A~ y = B y
     TRY(dense_mv_t(c, c.B2t, s, n, L.x, s, c.nvec, n, pdone));
@@ -1336,6 +1369,7 @@ msp_status gen_op1(SolveCtx& c, const double* p, double* q, double* t, const int
 msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int max_outer, bool normal) {
   Level& L = c.L1;
   const int64_t m = c.m, n = c.n, k = c.k;
+  ++L.S.seq;
   if (normal) {
     MSP_CHECK_HIP(fcg_init(c.st, L.S, n, B, ldb, L.r, L.x, nullptr, c.df + SLOT_L1));
   } else {
@@ -1345,10 +1379,11 @@ msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
   }
   TRY(gen_solve_m1(c, L.r, L.z));
   MSP_CHECK_HIP(fcg_first_dir(c.st, L.S, n, L.r, L.z, L.p));
-  int it = 0;
+  int it = 0, active = 0, iters = 0;
   while (true) {
-    TRY(sync(c));
-    if (*slot(c, SLOT_L1) == 0) {
+    TRY(wait_decision(c, L, SLOT_L1, &active, &iters));
+    if (active == 0) {
+      ++L.S.seq;
       if (normal) {
         // rtrue = B - (A^T A + lam I) x
         TRY(sweep(c, c.A_cf, c.cf_t, m, n, L.x, n, c.tvec, m, false, nullptr, false, true, false));
@@ -1361,8 +1396,8 @@ msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
         MSP_CHECK_HIP(launch_axpby(c.st, m, k, 1.0, B, ldb, -1.0, c.tvec, m, c.tvec, m, nullptr));
         MSP_CHECK_HIP(fcg_confirm(c.st, L.S, m, c.tvec, c.rho, tol, c.relres, c.df + SLOT_L1));
       }
-      TRY(sync(c));
-      if (*slot(c, SLOT_L1) == 0) break;
+      TRY(wait_decision(c, L, SLOT_L1, &active, &iters));
+      if (active == 0) break;
       c.acc.restarts += 1;
       if (!normal) TRY(sweep_t(c, c.A_sw, c.sw_t, m, n, c.rho, m, L.r, n, L.S.done));
       TRY(gen_solve_m1(c, L.r, L.z));
@@ -1371,6 +1406,7 @@ msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
     }
     if (it >= max_outer) break;
     TRY(gen_op1(c, L.p, L.q, c.tvec, L.S.done));
+    ++L.S.seq;
     if (normal) {
       MSP_CHECK_HIP(fcg_step(c.st, L.S, n, L.x, L.r, L.ro, L.p, L.q, 0.0, nullptr, tol, max_outer, c.df + SLOT_L1));
     } else {
@@ -1385,7 +1421,7 @@ msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
       fprintf(stderr, "[msp] level 1: %d steps, %lld level-2, %lld level-3 so far\n", it,
               (long long)c.acc.inner_iters, (long long)c.acc.level3_iters);
   }
-  c.acc.outer_iters += (int32_t)*slot(c, SLOT_L1 + 1);
+  c.acc.outer_iters += iters;
   return MSP_OK;
 }
 
@@ -1703,6 +1739,8 @@ msp_status make_ctx(SolveCtx& c, void* stream, const msp_precond* P, const void*
   if (inner_cap > kPcgMaxIter) c.use_p = false;
   *slot(c, SLOT_FAIL) = 0;
   if (c.use_p) MSP_CHECK_HIP(pcg_reset(c.st, c.pcg));
+  // decisions of earlier solves (their streams were synchronised) are numbered 0 from here
+  for (int i : {SLOT_L1, SLOT_L2}) *slot(c, i + 2) = *slot(c, i + 3) = 0;
   for (Level* L : {&c.L0, &c.L1, &c.L2, &c.L3}) MSP_CHECK_HIP(hipMemsetAsync(L->S.counter, 0, sizeof(int32_t), c.st));
   MSP_CHECK_HIP(hipMemsetAsync(c.l2b, 0, sizeof(double) * l2_bpart_doubles(c.s, k), c.st));
   return MSP_OK;

@@ -219,6 +219,13 @@ hipError_t launch_small_mv(hipStream_t st, int64_t s, const double* M, const dou
 // done[j]: 0 active, 1 converged (recurrence), 2 breakdown, 3 iteration cap,
 //          4 converged and confirmed on the recomputed residual.
 // ---------------------------------------------------------------------------------
+// Host mirror of a decision (mirror: four 32-bit words, 16-byte aligned, host-mapped): [0] columns
+// still iterating, [1] most iterations, read after a stream synchronisation; [2..3] as one word
+// the decision's number, the active count and the iterations, which the host may poll.
+constexpr int kSeqBits = 20;
+inline __host__ __device__ uint64_t decision_word(uint32_t seq, int32_t active, int32_t iters) {
+  return ((uint64_t)(seq & ((1u << kSeqBits) - 1)) << 44) | ((uint64_t)(uint32_t)active << 32) | (uint32_t)iters;
+}
 struct FcgState {
   double* rz;
   double* rz_next;   // the other of the two rz buffers (fcg_direction exchanges them)
@@ -235,6 +242,7 @@ struct FcgState {
   int32_t* done_next;   // [k] decision taken inside a multi-block kernel, committed by the next
   int32_t* iters_next;  // [k] single-block kernel (so no block reads a value another block rewrites)
   int64_t k;
+  uint32_t seq = 0;     // number of the decision that the next deciding kernel publishes
 };
 size_t fcg_part_doubles(int64_t len, int64_t k);
 FcgState carve_fcg_state(WsCarver& w, int64_t len, int64_t k);
