@@ -15,7 +15,8 @@
 // and column groups give too few wavefronts to keep HBM busy (a few right-hand sides),
 // the reduction range is split into segments: each wavefront writes its partial tile and
 // a second kernel adds the segments of every output in a fixed order, applies the shift
-// and writes the dot partials.
+// and writes the dot partials. The shift is a term ca V beside cb A X: with V another block of
+// vectors the same kernels give z = (r - C y) / lam~ of SolveM1.
 #include "msp_internal.h"
 
 #include <hip/hip_bf16.h>
@@ -130,10 +131,20 @@ __device__ __forceinline__ void ld_x(const double* p, TC* o) {
   }
 }
 
+// Y = cb A X + ca V (V null: A X alone)
+struct GemmAdd {
+  const double* V;
+  int64_t ldv;
+  double ca, cb;
+  __device__ __forceinline__ double of(double ax, int j, int row) const {
+    return V ? fma(cb, ax, ca * V[(int64_t)j * ldv + row]) : ax;
+  }
+};
+
 template <class TA, class TC, int RT, int KT>
 __global__ void __launch_bounds__(256) k_gemm(const TA* __restrict__ A, int64_t lda, int rows, int cols,
                                              const double* __restrict__ X, int64_t ldx, double* __restrict__ Y,
-                                             int64_t ldy, int k, double lam, int diag,
+                                             int64_t ldy, int k, GemmAdd add,
                                              const int32_t* __restrict__ skip, double* __restrict__ dot_part,
                                              int nrs, int ncs, int nseg, int seg_cols, double* __restrict__ part) {
   using L = Ld<TA, TC>;
@@ -225,8 +236,8 @@ __global__ void __launch_bounds__(256) k_gemm(const TA* __restrict__ A, int64_t 
         for (int e = 0; e < 4; ++e) {
           const int row = r0 + 16 * t + out_row<TC>(g, e);
           if (row < rows) {
-            const double xr = (diag || dot_part) ? X[(int64_t)j * ldx + row] : 0.0;
-            const double y = (double)acc[t][q][e] + (diag ? lam * xr : 0.0);
+            const double xr = dot_part ? X[(int64_t)j * ldx + row] : 0.0;
+            const double y = add.of((double)acc[t][q][e], j, row);
             Y[(int64_t)j * ldy + row] = y;
             dp = fma(xr, y, dp);
           }
@@ -244,15 +255,15 @@ __global__ void __launch_bounds__(256) k_gemm(const TA* __restrict__ A, int64_t 
 // Y[:, j] = sum over the segments (fixed order) (+ lam X[:, j]); dot partials per 64 rows
 __global__ void __launch_bounds__(WAVE) k_gemm_sum(const double* __restrict__ part, int nseg, int rows, int k,
                                                   const double* __restrict__ X, int64_t ldx, double* __restrict__ Y,
-                                                  int64_t ldy, double lam, int diag, const int32_t* __restrict__ skip,
+                                                  int64_t ldy, GemmAdd add, const int32_t* __restrict__ skip,
                                                   double* __restrict__ dot_part) {
   const int row = blockIdx.x * WAVE + threadIdx.x, j = blockIdx.y;
   double dp = 0.0;
   if (!(skip && skip[j]) && row < rows) {
     double acc = 0.0;
     for (int s = 0; s < nseg; ++s) acc += part[((int64_t)s * k + j) * rows + row];
-    const double xr = (diag || dot_part) ? X[(int64_t)j * ldx + row] : 0.0;
-    const double y = acc + (diag ? lam * xr : 0.0);
+    const double xr = dot_part ? X[(int64_t)j * ldx + row] : 0.0;
+    const double y = add.of(acc, j, row);
     Y[(int64_t)j * ldy + row] = y;
     dp = xr * y;
   }
@@ -283,7 +294,7 @@ int gemm_segments(int64_t rows, int64_t cols, int k, int64_t waves, size_t scrat
 
 template <class TA, class TC, int RT, int KT>
 hipError_t gemm_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X,
-                  int64_t ldx, double* Y, int64_t ldy, int k, double lam, bool diag, const int32_t* skip,
+                  int64_t ldx, double* Y, int64_t ldy, int k, GemmAdd add, const int32_t* skip,
                   double* dot_part, int* nblocks, double* scratch, size_t scratch_doubles, int min_seg,
                   int force_nseg, int* nseg_out, bool defer_sum) {
   static_assert(16 * RT == WAVE, "the segment sum takes 64-row sets");
@@ -300,10 +311,10 @@ hipError_t gemm_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
   const int64_t waves = (int64_t)nrs * ncs * nseg;
   const unsigned blocks = (unsigned)((waves + 3) / 4);
   hipLaunchKernelGGL((k_gemm<TA, TC, RT, KT>), dim3(blocks), dim3(256), 0, st, A, lda, (int)rows, (int)cols, X, ldx, Y,
-                     ldy, k, lam, diag ? 1 : 0, skip, dot_part, nrs, ncs, nseg, seg_cols, scratch);
+                     ldy, k, add, skip, dot_part, nrs, ncs, nseg, seg_cols, scratch);
   if (nseg > 1 && !defer_sum)
     hipLaunchKernelGGL(k_gemm_sum, dim3((unsigned)nrs, (unsigned)k), dim3(WAVE), 0, st, scratch, nseg, (int)rows, k, X,
-                       ldx, Y, ldy, lam, diag ? 1 : 0, skip, dot_part);
+                       ldx, Y, ldy, add, skip, dot_part);
   if (nblocks) *nblocks = nrs;
   if (nseg_out) *nseg_out = nseg;
   return hipGetLastError();
@@ -313,16 +324,16 @@ hipError_t gemm_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
 // keeping the accumulators in registers
 template <class TA, class TC>
 hipError_t gemm_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X, int64_t ldx,
-                  double* Y, int64_t ldy, int k, double lam, bool diag, const int32_t* skip, double* dot_part,
+                  double* Y, int64_t ldy, int k, GemmAdd add, const int32_t* skip, double* dot_part,
                   int* nblocks, double* scratch, size_t scratch_doubles, int min_seg = kSegSweep, int force_nseg = 0,
                   int* nseg_out = nullptr, bool defer_sum = false) {
   if (k <= 16)
-    return gemm_t<TA, TC, 4, 1>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks, scratch,
+    return gemm_t<TA, TC, 4, 1>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, add, skip, dot_part, nblocks, scratch,
                                 scratch_doubles, min_seg, force_nseg, nseg_out, defer_sum);
   if (sizeof(TC) == 8 || k <= 32)
-    return gemm_t<TA, TC, 4, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks, scratch,
+    return gemm_t<TA, TC, 4, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, add, skip, dot_part, nblocks, scratch,
                                 scratch_doubles, min_seg, force_nseg, nseg_out, defer_sum);
-  return gemm_t<TA, TC, 4, 4>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks, scratch,
+  return gemm_t<TA, TC, 4, 4>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, add, skip, dot_part, nblocks, scratch,
                               scratch_doubles, min_seg, force_nseg, nseg_out, defer_sum);
 }
 
@@ -360,7 +371,27 @@ __global__ void __launch_bounds__(256) k_gemm_t(const TA* __restrict__ A, int64_
   for (int m = 0; m < VEC; ++m)
 #pragma unroll
     for (int q = 0; q < KT; ++q) acc[m][q] = typename V4<TC>::t{0, 0, 0, 0};
-  for (int r = rb; r < re; r += 4) {
+  int r = rb;
+  if (c0 + 16 * VEC <= cols) {  // whole column tile: four steps' loads in flight
+    constexpr int U = 4;
+    for (; r + 4 * U <= re; r += 4 * U) {
+      TC a[U][VEC], b[U][KT];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int row = r + 4 * u + g;
+        L::vec(A + (int64_t)row * lda + cl, a[u]);
+#pragma unroll
+        for (int q = 0; q < KT; ++q) b[u][q] = (TC)xp[q][row];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int m = 0; m < VEC; ++m)
+#pragma unroll
+          for (int q = 0; q < KT; ++q) acc[m][q] = mfma(a[u][m], b[u][q], acc[m][q]);
+    }
+  }
+  for (; r < re; r += 4) {
     const int row = r + g;
     const bool ok = row < re;
     TC a[VEC], b[KT];
@@ -403,16 +434,23 @@ __global__ void k_sum_splits_t(const double* __restrict__ part, int nsplit, int6
   const int64_t c = idx % cols;
   if (skip && skip[j]) return;
   double acc = 0.0;
-  for (int t = 0; t < nsplit; ++t) acc += part[(int64_t)t * len + idx];
+  for (int t0 = 0; t0 < nsplit; t0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = t0 + u < nsplit ? part[(int64_t)(t0 + u) * len + idx] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += v[u];
+  }
   Y[(int64_t)j * ldy + c] = acc;
 }
 
-// row splits of the transposed product: enough wavefronts to fill the chip
+// row splits of the transposed product: enough wavefronts to fill the chip, 64 rows or more
+// each
 void gemmT_split(int64_t rows, int64_t cols, int k, int vec, int kt, int* nsplit_out, int* rps_out) {
   const int64_t nct = (cols + 16 * vec - 1) / (16 * vec);
   const int64_t ncs = ((k + 15) / 16 + kt - 1) / kt;
   int64_t nsplit = (2048 + nct * ncs - 1) / (nct * ncs);
-  nsplit = std::max<int64_t>(1, std::min<int64_t>(nsplit, std::min<int64_t>(64, (rows + 255) / 256)));
+  nsplit = std::max<int64_t>(1, std::min<int64_t>(nsplit, std::min<int64_t>(64, (rows + 63) / 64)));
   const int64_t rps = ((rows + nsplit - 1) / nsplit + 3) / 4 * 4;
   *nsplit_out = (int)((rows + rps - 1) / rps);
   *rps_out = (int)rps;
@@ -441,6 +479,15 @@ hipError_t gemmT_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int6
   return hipGetLastError();
 }
 
+// one 16-column group per wavefront up to 16 columns (two would multiply sixteen columns of
+// zeros), else two
+template <class TA, class TC>
+hipError_t gemmT_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X, int64_t ldx,
+                   double* Y, int64_t ldy, int k, const int32_t* skip, double* part) {
+  if (k <= 16) return gemmT_t<TA, TC, 1>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, skip, part);
+  return gemmT_t<TA, TC, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, skip, part);
+}
+
 }  // namespace
 
 int gemm_row_sets(int64_t rows) { return (int)((rows + 63) / 64); }
@@ -449,7 +496,7 @@ size_t gemm_t_part_doubles(int64_t rows, int64_t cols, int64_t k) {
   size_t worst = 0;
   for (int vec : {2, 4, 8}) {
     int ns = 1, rps = 4;
-    gemmT_split(rows, cols, (int)k, vec, 2, &ns, &rps);
+    gemmT_split(rows, cols, (int)k, vec, k <= 16 ? 1 : 2, &ns, &rps);
     if (ns > 1) worst = std::max(worst, (size_t)ns * k * cols);
   }
   return worst + 64;
@@ -461,12 +508,12 @@ hipError_t launch_gemm_t(hipStream_t st, const void* A, msp_dtype a_t, int64_t r
   const int kk = (int)k;
   switch (a_t) {
     case MSP_F64:
-      return gemmT_t<double, double, 2>(st, (const double*)A, rows, cols, lda, X, ldx, Y, ldy, kk, skip, part);
+      return gemmT_k<double, double>(st, (const double*)A, rows, cols, lda, X, ldx, Y, ldy, kk, skip, part);
     case MSP_F32:
-      return gemmT_t<float, float, 2>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, skip, part);
+      return gemmT_k<float, float>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, skip, part);
     case MSP_BF16:
-      return gemmT_t<__hip_bfloat16, float, 2>(st, (const __hip_bfloat16*)A, rows, cols, lda, X, ldx, Y, ldy, kk,
-                                                skip, part);
+      return gemmT_k<__hip_bfloat16, float>(st, (const __hip_bfloat16*)A, rows, cols, lda, X, ldx, Y, ldy, kk, skip,
+                                            part);
   }
   return hipErrorInvalidValue;
 }
@@ -474,7 +521,7 @@ hipError_t launch_gemm_t(hipStream_t st, const void* A, msp_dtype a_t, int64_t r
 hipError_t launch_gemm_t_f32_as_f64(hipStream_t st, const float* A, int64_t rows, int64_t cols, int64_t lda,
                                     const double* X, int64_t ldx, double* Y, int64_t ldy, int64_t k,
                                     const int32_t* skip, double* part) {
-  return gemmT_t<float, double, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, (int)k, skip, part);
+  return gemmT_k<float, double>(st, A, rows, cols, lda, X, ldx, Y, ldy, (int)k, skip, part);
 }
 
 hipError_t launch_gemm_split(hipStream_t st, const void* A, msp_dtype a_t, bool fp64_arith, int64_t rows,
@@ -482,19 +529,20 @@ hipError_t launch_gemm_split(hipStream_t st, const void* A, msp_dtype a_t, bool 
                              double lam, bool diag, const int32_t* skip, double* dot_part, int* nblocks,
                              double* scratch, size_t scratch_doubles, int nseg) {
   const int kk = (int)k;
+  const GemmAdd add{diag ? X : nullptr, ldx, lam, 1.0};
   switch (a_t) {
     case MSP_F64:
-      return gemm_k<double, double>(st, (const double*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam, diag, skip,
+      return gemm_k<double, double>(st, (const double*)A, rows, cols, lda, X, ldx, Y, ldy, kk, add, skip,
                                     dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
     case MSP_F32:
       if (fp64_arith)
-        return gemm_k<float, double>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam, diag, skip,
+        return gemm_k<float, double>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, add, skip,
                                      dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
-      return gemm_k<float, float>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam, diag, skip, dot_part,
+      return gemm_k<float, float>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, kk, add, skip, dot_part,
                                   nblocks, scratch, scratch_doubles, kSegSweep, nseg);
     case MSP_BF16:
-      return gemm_k<__hip_bfloat16, float>(st, (const __hip_bfloat16*)A, rows, cols, lda, X, ldx, Y, ldy, kk, lam,
-                                           diag, skip, dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
+      return gemm_k<__hip_bfloat16, float>(st, (const __hip_bfloat16*)A, rows, cols, lda, X, ldx, Y, ldy, kk, add,
+                                           skip, dot_part, nblocks, scratch, scratch_doubles, kSegSweep, nseg);
   }
   return hipErrorInvalidValue;
 }
@@ -520,6 +568,20 @@ size_t gemm_split_doubles(int64_t rows, int64_t k) { return (size_t)16 * rows * 
 hipError_t launch_gemm_seg(hipStream_t st, const double* M, int64_t rows, int64_t cols, const double* X,
                            int64_t ldx, double* Y, int64_t ldy, int64_t k, const int32_t* skip, double* scratch,
                            size_t scratch_doubles, int min_seg, int* nseg_out, bool defer_sum) {
-  return gemm_k<double, double>(st, M, rows, cols, cols, X, ldx, Y, ldy, (int)k, 0.0, false, skip, nullptr, nullptr,
+  return gemm_k<double, double>(st, M, rows, cols, cols, X, ldx, Y, ldy, (int)k, GemmAdd{}, skip, nullptr, nullptr,
                                 scratch, scratch_doubles, min_seg, 0, nseg_out, defer_sum);
+}
+
+hipError_t launch_gemm_add(hipStream_t st, const void* A, msp_dtype a_t, int64_t rows, int64_t cols, int64_t lda,
+                           const double* X, int64_t ldx, double* Y, int64_t ldy, int64_t k, double ca,
+                           const double* V, int64_t ldv, double cb, const int32_t* skip, double* scratch,
+                           size_t scratch_doubles) {
+  const GemmAdd add{V, ldv, ca, cb};
+  if (a_t == MSP_F64)
+    return gemm_k<double, double>(st, (const double*)A, rows, cols, lda, X, ldx, Y, ldy, (int)k, add, skip, nullptr,
+                                  nullptr, scratch, scratch_doubles);
+  if (a_t == MSP_F32)
+    return gemm_k<float, double>(st, (const float*)A, rows, cols, lda, X, ldx, Y, ldy, (int)k, add, skip, nullptr,
+                                 nullptr, scratch, scratch_doubles);
+  return hipErrorInvalidValue;
 }

@@ -118,8 +118,30 @@ __global__ void __launch_bounds__(256) k_l2_op(const TY* __restrict__ Y, int64_t
       acc[g][q] = 0.0;
     }
   }
-  // two rows per step for memory-level parallelism
   int64_t r = r0 + w;
+  // the right-hand side pass: four rows in flight, loads without branches (a column beyond s
+  // repeats the last one; its sum is not stored)
+  if constexpr (MODE == 1 && KG == 1 && CPL <= 16) {
+    int cc[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) cc[q] = min(lane + q * WAVE, s - 1);
+    for (; r + 12 < r1; r += 16) {
+      TY y[4][CPL];
+      double t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const TY* row = Y + (r + 4 * u) * ldy_;
+        t[u] = v[(int64_t)j0 * ldv + r + 4 * u];
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) y[u][q] = row[cc[q]];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) acc[0][q] = fma((double)y[u][q], live[0] ? t[u] : 0.0, acc[0][q]);
+    }
+  }
+  // two rows per step for memory-level parallelism
   for (; r + 4 < r1; r += 8) {
     double ya[CPL], yb[CPL];
 #pragma unroll

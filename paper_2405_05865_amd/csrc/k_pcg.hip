@@ -12,7 +12,8 @@
 // per thread) and evaluates all dots and scalars itself, with the same code on the same data,
 // so the blocks agree bit for bit and exchange nothing but the rows of the products. With
 // s <= 128 one block holds both operands and a step has no exchange at all; larger s takes
-// s / 32 blocks (s <= 512 and four columns: s / 32; s <= 1024: s / 16).
+// s / 32 blocks, with few columns s / 16 (after a sweep of a large matrix the operands come from
+// HBM, 256 KB per block at s = 512 with s / 32), and s / 16 for s > 512.
 //
 // Exchange. The rows go through a buffer of 64-bit words, half of a double beside the 32-bit
 // number of the exchange: a reader polls the words themselves until the number is right, so a
@@ -253,7 +254,6 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
   const int oc = KC == 1 ? 0 : min(tid, KC - 1);
   if (tid == 0) sh.stop = 0;
   double hm[RPW][CPL], mm[RPW][CPL];
-  B::load_rows(a.H, s, row0, hm);
   double r[EPT], y[EPT], p[EPT], u[EPT];
   double v2[2][EPT], v1[1][EPT];
 #pragma unroll
@@ -262,6 +262,7 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
 #pragma unroll
     for (int q = 0; q < EPT; ++q)
       if (ein[q]) y[q] += a.rhs[(int64_t)g * a.k * s + eo[q]];
+  B::load_rows(a.H, s, row0, hm);  // behind the right-hand side: loads return in order
 
   auto stage = [&](const double(&x)[EPT]) {
 #pragma unroll
@@ -514,11 +515,11 @@ hipError_t dispatch(hipStream_t st, const PcgArgs& a, const PcgShape& h, int gro
   switch (h.cpl * 100 + h.kc) {
     case 101: return go<MODE, 1, 8, 1, false>(st, a, groups);
     case 201: return go<MODE, 2, 16, 1, false>(st, a, groups);
-    case 401: return go<MODE, 4, 4, 1, true>(st, a, groups);
+    case 401: return h.rpw == 2 ? go<MODE, 4, 2, 1, true>(st, a, groups) : go<MODE, 4, 4, 1, true>(st, a, groups);
     case 402: return go<MODE, 4, 4, 2, true>(st, a, groups);
     case 404: return go<MODE, 4, 4, 4, true>(st, a, groups);
     case 408: return go<MODE, 4, 4, 8, true>(st, a, groups);
-    case 801: return go<MODE, 8, 4, 1, true>(st, a, groups);
+    case 801: return h.rpw == 2 ? go<MODE, 8, 2, 1, true>(st, a, groups) : go<MODE, 8, 4, 1, true>(st, a, groups);
     case 802: return go<MODE, 8, 4, 2, true>(st, a, groups);
     case 804: return go<MODE, 8, 4, 4, true>(st, a, groups);
     case 1601: return go<MODE, 16, 2, 1, true>(st, a, groups);
@@ -536,6 +537,14 @@ PcgShape pcg_shape(int64_t s, int64_t k) {
   h.cpl = chunks <= 1 ? 1 : chunks <= 2 ? 2 : chunks <= 4 ? 4 : chunks <= 8 ? 8 : 16;
   const int rpw = h.cpl == 1 ? 8 : h.cpl == 2 ? 16 : h.cpl == 16 ? 2 : 4;
   h.nblk = (int)((s + NWV * rpw - 1) / (NWV * rpw));
+  h.rpw = rpw;
+  if (rpw == 4) {  // few columns: twice the blocks, each fetching half as much of the operands
+    const int nb2 = (int)((s + NWV * 2 - 1) / (NWV * 2));
+    if (k * nb2 <= kPcgMaxBlocks) {
+      h.rpw = 2;
+      h.nblk = nb2;
+    }
+  }
   // the fewest columns per group (1, 2, 4, 8) with which the groups fit one launch; at most
   // what the registers hold beside the operands (8 for s <= 256, 4 for s <= 512, else 2)
   const int most = h.cpl <= 2 ? 1 : (h.cpl == 4 ? 8 : (h.cpl == 8 ? 4 : 2));

@@ -1119,6 +1119,16 @@ msp_status build_explicit(SolveCtx& c) {
   return invert_h2(c);
 }
 
+// Y^T X in FP64 arithmetic for either storage of the sketch
+hipError_t launch_gemm_t_f64(hipStream_t st, const void* Y, int64_t rows, int64_t cols, int64_t ld, const double* X,
+                             int64_t ldx, double* out, int64_t ldo, int64_t k, const int32_t* skip, double* part) {
+  return launch_gemm_t(st, Y, MSP_F64, rows, cols, ld, X, ldx, out, ldo, k, skip, part);
+}
+hipError_t launch_gemm_t_f32(hipStream_t st, const void* Y, int64_t rows, int64_t cols, int64_t ld, const double* X,
+                             int64_t ldx, double* out, int64_t ldo, int64_t k, const int32_t* skip, double* part) {
+  return launch_gemm_t_f32_as_f64(st, (const float*)Y, rows, cols, ld, X, ldx, out, ldo, k, skip, part);
+}
+
 // ---------------------------------- PSD (Algorithms 1-2) ----------------------------
 // z = (r - C y^) / lam~ with y^ from level-2 FCG on (C^T C + lam~ W) y = C^T r, M2^{-1}
 msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
@@ -1126,8 +1136,16 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
   const int64_t s = c.s, n = c.n, k = c.k;
   const int32_t* pdone = c.L1.S.done;
   L2Step a = l2step_for(c, c.L2, P->Minv, P->Wm, P->lt, 0.0, c.o->inner_tol, c.o->max_inner, SLOT_L2, pdone);
-  MSP_CHECK_HIP(l2_op(c.st, P->Y, P->y_t, n, s, P->ldy, r, n, k, pdone, a.part, nullptr, nullptr, nullptr, nullptr,
-                      true));
+  // with eight columns or more both passes over C are matrix-core products (one read of C
+  // each, where the column groups of the row kernels read it k / 4 times: n = 10007, s = 320, 16
+  // columns: 39 + 62 us for C^T r and r - C y, YBLOCK us as products)
+  const bool block = c.use_p && k >= kGemmMinK;
+  if (block)
+    MSP_CHECK_HIP((P->y_t == MSP_F64 ? launch_gemm_t_f64 : launch_gemm_t_f32)(c.st, P->Y, n, s, P->ldy, r, n, c.rhs2, s,
+                                                                              k, pdone, c.gpart));
+  else
+    MSP_CHECK_HIP(l2_op(c.st, P->Y, P->y_t, n, s, P->ldy, r, n, k, pdone, a.part, nullptr, nullptr, nullptr, nullptr,
+                        true));
   if (c.form == 2) {  // y = (C^T C + lam~ W)^{-1} C^T r exactly
     MSP_CHECK_HIP(l2_reduce_to(c.st, a, c.rhs2, pdone));
     MSP_CHECK_HIP(launch_small_mv(c.st, s, c.H2, c.rhs2, k, pdone, c.L2.x));
@@ -1140,14 +1158,18 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
     p.H = c.G2;
     p.Minv[0] = P->Minv;
     p.nsol = 1;
-    p.rhs = l2_groups(a, &p.nrhs);
+    if (block) p.rhs = c.rhs2;
+    else p.rhs = l2_groups(a, &p.nrhs);
     p.out = c.L2.x;
     p.parent_done = pdone;
     p.tol = c.o->inner_tol;
     p.max_iter = c.o->max_inner;
     p.fail_mirror = c.df + SLOT_FAIL;
     MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, 0));
-    MSP_CHECK_HIP(
+    if (block)
+      MSP_CHECK_HIP(launch_gemm_add(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, s, z, n, k, 1.0 / P->lt, r, n,
+                                    -1.0 / P->lt, pdone, c.gemmpart, c.gemmpart_n));
+    else MSP_CHECK_HIP(
         launch_y_z(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, k, 1.0 / P->lt, r, n, -1.0 / P->lt, pdone, z, n));
     return MSP_OK;
   }

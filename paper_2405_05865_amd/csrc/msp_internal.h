@@ -168,6 +168,11 @@ int sketch_rows_choice(msp_dtype a_t, int64_t m, int64_t n, int64_t lda, int64_t
 hipError_t launch_gemm_seg(hipStream_t st, const double* M, int64_t rows, int64_t cols, const double* X,
                            int64_t ldx, double* Y, int64_t ldy, int64_t k, const int32_t* skip, double* scratch,
                            size_t scratch_doubles, int min_seg, int* nseg_out = nullptr, bool defer_sum = false);
+// Y[:, j] = ca V[:, j] + cb A X[:, j] in FP64 arithmetic on F64 or F32 storage (k >= kGemmMinK)
+hipError_t launch_gemm_add(hipStream_t st, const void* A, msp_dtype a_t, int64_t rows, int64_t cols, int64_t lda,
+                           const double* X, int64_t ldx, double* Y, int64_t ldy, int64_t k, double ca,
+                           const double* V, int64_t ldv, double cb, const int32_t* skip, double* scratch,
+                           size_t scratch_doubles);
 constexpr int kSegSmall = 64;
 constexpr int kSegWide = 256;
 constexpr int kSegSweep = 192;
@@ -441,6 +446,7 @@ constexpr int kPcgMaxIter = 1 << 24;   // exchanges of a launch are numbered in 
 constexpr int64_t kPcgWait = 5000000;  // 50 ms of the 100 MHz wall clock
 struct PcgShape {
   int cpl;       // 64-column chunks (1, 2, 4, 8, 16); 0: not supported
+  int rpw;       // operand rows per wavefront
   int nblk;      // blocks per group
   int kc;        // columns per group
   int groups;    // groups of the k columns
