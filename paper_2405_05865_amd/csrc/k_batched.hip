@@ -28,6 +28,7 @@
 // waits are bounded by wall-clock time: a slice that no helper claims in time is taken
 // by the leader, and an idle helper leaves.
 #include "msp_batched.h"
+#include "wave_ops.h"
 
 #include <hip/hip_bf16.h>
 
@@ -46,6 +47,9 @@ static_assert(CHR == NW * 16 * CRT, "a chunk is one tile row set per wavefront")
 constexpr uint64_t CLAIM_TICKS = 10000;       // 100 us: a live helper claims its slice sooner
 constexpr uint64_t SLICE_TICKS = 500000000;   // 5 s: a claimed slice must be done by then
 constexpr uint64_t IDLE_TICKS = 200000000;    // 2 s without a new epoch: the helper leaves
+
+constexpr int L2S = 256;  // largest s of the level-2 solve on LDS and registers
+static_assert(L2S == 16 * NW, "one 16-row tile per wavefront");
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -315,7 +319,7 @@ struct Ctx {
   float* pf;
   Cols *CH, *C1, *C2;
   double lam_lo;  // shift of the low-precision sweeps: lam, plus delta under refinement
-  double* red;   // [NW][256]
+  double* vx;    // LDS: [L2S][KB] block of s-vectors (level2_lds)
   double* part;  // [NW][KB]
   int* shi;      // [8] LDS ints for broadcasts
   int epoch;     // thread 0: last published sweep epoch
@@ -680,11 +684,168 @@ struct Batch {
     return m;
   }
 
+  // ---- the level-2 iteration for s <= L2S ------------------------------------------
+  // Wavefront j keeps all the vectors of column j in registers (element lane + 64 m); the
+  // only traffic of a step is the two s x s operands from L2, one 16-row tile per wavefront, and
+  // the multiplied block and the product through one LDS buffer. The block is stored as
+  // [element][column] with the columns rotated by the element, which keeps both the element-wise
+  // accesses (a wavefront's own column) and the matrix-core operands (16 columns of an element)
+  // off each other's banks. Bound by the FP64 matrix cores of one compute unit (6.8 us per
+  // product at s = 256). s = 256, 16 columns: 103 us per step with the vectors in global memory,
+  // L2STEP us with this.
+  static __device__ __forceinline__ int vx_at(int e, int col) { return e * KB + ((col + e) & (KB - 1)); }
+
+  // out = M x (x, out: element lane + 64 m of the wavefront's column); called by all wavefronts
+  static __device__ void smv_lds(Ctx& c, const double* __restrict__ M, const double (&x)[4], double (&out)[4]) {
+    const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
+    const int s = c.s;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) c.vx[vx_at(lane + WAVE * m, w)] = x[m];  // zero beyond s
+    __syncthreads();
+    v4d acc = {0, 0, 0, 0};
+    if (16 * w < s) {  // whole wavefronts
+      // 16-byte loads at element alignment (any s)
+      typedef double u2 __attribute__((ext_vector_type(2), aligned(8)));
+      const double* row = M + (int64_t)min(16 * w + i, s - 1) * s;
+      auto mul = [&](double a0, double a1, int e) {
+        acc = mfma(a0, c.vx[vx_at(e, i)], acc);
+        acc = mfma(a1, c.vx[vx_at(e + 1, i)], acc);
+      };
+      constexpr int U = 8;
+      int c0 = 0;
+      for (; c0 + 8 * U <= s; c0 += 8 * U) {
+        u2 a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = *gv<u2>(row + c0 + 8 * u + 2 * g);
+#pragma unroll
+        for (int u = 0; u < U; ++u) mul(a[u].x, a[u].y, c0 + 8 * u + 2 * g);
+      }
+      for (; c0 < s; c0 += 8) {  // elements beyond s are zero in LDS; columns stay in the row
+        const int e = c0 + 2 * g;
+        const double a0 = row[min(e, s - 1)], a1 = row[min(e + 1, s - 1)];
+        mul(a0, a1, e);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c.vx[vx_at(16 * w + out_row<double>(g, e), i)] = acc[e];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int e = lane + WAVE * m;
+      out[m] = e < s ? c.vx[vx_at(e, w)] : 0.0;
+    }
+    __syncthreads();
+  }
+
+  static __device__ void level2_lds(Ctx& c) {
+    using wave_ops::wave_sum;
+    const int w = wave_id(), lane = lane_id();
+    Cols* D = c.C2;
+    double r[4], ro[4], z[4], p[4], q[4], y[4];
+    double bn = 0.0, rz = 0.0;
+    int itj = 0;
+    int dj = 4;
+    {
+      const bool act = w < c.k && c.C1->done[w] == 0;
+      double acc = 0.0;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int e = lane + WAVE * m;
+        r[m] = (act && e < c.s) ? c.b2[(int64_t)w * c.lds + e] : 0.0;
+        y[m] = p[m] = 0.0;
+        acc = fma(r[m], r[m], acc);
+      }
+      bn = sqrt(wave_sum(acc));
+      dj = (!act || bn == 0.0) ? 4 : 0;
+      if (lane == 0) D->done[w] = dj;  // (Cols holds KB = NW columns)
+    }
+    const uint64_t l2t0 = (c.P.profile && threadIdx.x == 0) ? wall_clock64() : 0;
+    smv_lds(c, c.S.Minv, r, z);
+    {
+      double acc = 0.0;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        p[m] = dj == 0 ? z[m] : 0.0;
+        acc = fma(r[m], z[m], acc);
+      }
+      rz = wave_sum(acc);
+    }
+    int it = 0;
+    while (it < c.P.max_inner) {
+      __syncthreads();
+      if (!any_active(D, NW)) break;
+      smv_lds(c, c.S.H, p, q);
+      if (dj == 0) {
+        double pq = 0.0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) pq = fma(p[m], q[m], pq);
+        pq = wave_sum(pq);
+        const bool brk = !(pq > 0.0);
+        const double al = brk ? 0.0 : rz / pq;
+        double acc = 0.0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          y[m] = fma(al, p[m], y[m]);
+          ro[m] = r[m];
+          r[m] = fma(-al, q[m], r[m]);
+          acc = fma(r[m], r[m], acc);
+        }
+        const double rn = sqrt(wave_sum(acc));
+        ++itj;
+        if (brk || !(rn == rn)) dj = 2;
+        else if (rn <= c.P.inner_tol * bn) dj = 1;
+        else if (itj >= c.P.max_inner) dj = 3;
+        if (lane == 0) D->done[w] = dj;
+      }
+      ++it;
+      __syncthreads();
+      if (!any_active(D, NW)) break;
+      smv_lds(c, c.S.Minv, r, z);
+      if (dj == 0) {
+        double zr = 0.0, zro = 0.0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          zr = fma(z[m], r[m], zr);
+          zro = fma(z[m], ro[m], zro);
+        }
+        zr = wave_sum(zr);
+        zro = wave_sum(zro);
+        if (rz != 0.0 && isfinite(rz)) {
+          const double beta = (zr - zro) / rz;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) p[m] = fma(beta, p[m], z[m]);
+          rz = zr;
+        } else {
+          dj = 2;  // beta's denominator vanished: breakdown, the iterate is kept
+          if (lane == 0) D->done[w] = dj;
+        }
+      }
+    }
+    if (w < c.k) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int e = lane + WAVE * m;
+        if (e < c.s) c.y2[(int64_t)w * c.lds + e] = y[m];
+      }
+    }
+    if (threadIdx.x == 0) {
+      c.inner += it;
+      if (c.P.profile) c.ticks[BT_LEVEL2] += wall_clock64() - l2t0;
+    }
+    __syncthreads();
+  }
+
   // ---- Algorithm 2: z1 = SolveM1(r1) for the columns active at level 1 -------------
   static __device__ void solve_m1(Ctx& c) {
     const int w = wave_id(), lane = lane_id();
     Cols* D = c.C2;
     yt_r(c);
+    if (c.s <= L2S) {
+      level2_lds(c);
+      y_z(c);
+      return;
+    }
     if (w < c.k) {
       const bool act = c.C1->done[w] == 0;
       double acc = 0.0;
@@ -1185,7 +1346,7 @@ template <class TLO, class THI, class TY>
 __global__ void __launch_bounds__(NTB) k_batch_psd(const BatchSys* __restrict__ sys, BatchPrm prm, int k,
                                                    BatchOut* __restrict__ out) {
   __shared__ Cols cH, c1, c2;
-  __shared__ double red[NW * 256];
+  __shared__ double vx[L2S * KB];
   __shared__ double part[NW * KB];
   __shared__ int shi[8];
   __shared__ JobSh js;
@@ -1229,7 +1390,7 @@ __global__ void __launch_bounds__(NTB) k_batch_psd(const BatchSys* __restrict__ 
   c.CH = &cH;
   c.C1 = &c1;
   c.C2 = &c2;
-  c.red = red;
+  c.vx = vx;
   c.part = part;
   c.outer = c.inner = c.refine = c.restarts = 0;
   for (int q = 0; q < BT_NPHASE; ++q) c.ticks[q] = 0;

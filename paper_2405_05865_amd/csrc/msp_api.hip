@@ -1138,7 +1138,7 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
   L2Step a = l2step_for(c, c.L2, P->Minv, P->Wm, P->lt, 0.0, c.o->inner_tol, c.o->max_inner, SLOT_L2, pdone);
   // with eight columns or more both passes over C are matrix-core products (one read of C
   // each, where the column groups of the row kernels read it k / 4 times: n = 10007, s = 320, 16
-  // columns: 39 + 62 us for C^T r and r - C y, YBLOCK us as products)
+  // columns: 39 + 62 us for C^T r and r - C y, 12 + 28 us as products)
   const bool block = c.use_p && k >= kGemmMinK;
   if (block)
     MSP_CHECK_HIP((P->y_t == MSP_F64 ? launch_gemm_t_f64 : launch_gemm_t_f32)(c.st, P->Y, n, s, P->ldy, r, n, c.rhs2, s,
