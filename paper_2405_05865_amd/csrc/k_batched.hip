@@ -22,11 +22,13 @@
 // Teams. One compute unit streams only about 1/256 of the chip's bandwidth, so a batch
 // is bound by its largest systems. A workgroup whose system is finished joins a larger
 // unfinished one as a helper: the system's workgroup (the leader) publishes every A-sweep
-// as an epoch in the system's team record, and the row range is cut into 512-row chunks
-// handed out as slices (the Y^T r and Y y passes of SolveM1 are team jobs too). Every chunk writes its own <x, A x> partials and the leader adds
-// them in chunk order, so the result is the same bits whoever computed which chunk. All
-// waits are bounded by wall-clock time: a slice that no helper claims in time is taken
-// by the leader, and an idle helper leaves.
+// as an epoch in the system's team record, and the row range is cut into 256-row chunks
+// handed out as slices (the Y^T r and Y y passes of SolveM1 are team jobs too). Where the
+// systems leave compute units free, further workgroups are launched as helpers from the
+// start. Every chunk writes its own <x, A x> partials and the leader adds them in chunk
+// order, so the result is the same bits whoever computed which chunk. All waits are bounded
+// by wall-clock time: a slice that no helper claims in time is taken by the leader, and an
+// idle helper leaves.
 #include "msp_batched.h"
 #include "wave_ops.h"
 
@@ -39,23 +41,24 @@ constexpr int NW = 16;           // wavefronts per workgroup
 constexpr int NTB = NW * WAVE;   // 1024 threads
 constexpr int KB = MSP_BATCH_KMAX;
 constexpr int MAX_RESTARTS = 8;
-constexpr int CRT = 2;              // 16-row MFMA tiles per wavefront and chunk
-constexpr int CHR = MSP_BATCH_CHR;  // rows per chunk: NW wavefronts x one 32-row tile
+constexpr int CHR = MSP_BATCH_CHR;  // rows per chunk: NW wavefronts x one 16-row tile
 constexpr int MAXH = MSP_BATCH_MAXH;
-static_assert(CHR == NW * 16 * CRT, "a chunk is one tile row set per wavefront");
+static_assert(CHR == NW * 16, "a chunk is one tile row per wavefront");
 // wall-clock (100 MHz) bounds of the team waits
 constexpr uint64_t CLAIM_TICKS = 10000;       // 100 us: a live helper claims its slice sooner
 constexpr uint64_t SLICE_TICKS = 500000000;   // 5 s: a claimed slice must be done by then
+constexpr uint64_t START_TICKS = 100000;      // 1 ms: every system of a launch that fits is running
 constexpr uint64_t IDLE_TICKS = 200000000;    // 2 s without a new epoch: the helper leaves
 
 constexpr int L2S = 256;  // largest s of the level-2 solve on LDS and registers
-static_assert(L2S == 16 * NW, "one 16-row tile per wavefront");
+static_assert(L2S == 16 * NW && KB == NW, "one 16-row tile and one column per wavefront");
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
-typedef double nd2 __attribute__((ext_vector_type(2)));
-typedef float nf4 __attribute__((ext_vector_type(4)));
-typedef uint32_t nu4 __attribute__((ext_vector_type(4)));
+// 16-byte loads at the alignment of the elements: rows of any length and pitch take them
+typedef double nd2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float nf4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t nu4 __attribute__((ext_vector_type(4), aligned(2)));
 
 template <class TC>
 struct V4;
@@ -98,7 +101,7 @@ __device__ __forceinline__ const __attribute__((address_space(1))) T* gv(const v
   return (const __attribute__((address_space(1))) T*)(p);
 }
 
-// Loads of VEC consecutive matrix elements (one 16-byte access when aligned), converted
+// Loads of VEC consecutive matrix elements (one 16-byte access), converted
 // to the arithmetic type TC.
 template <class TA, class TC>
 struct Ld;
@@ -113,7 +116,7 @@ struct Ld<double, double> {
     o[0] = v.x;
     o[1] = v.y;
   }
-  __device__ static double one(const double* p) { return *p; }
+  __device__ static double one(const double* p) { return *gv<double>(p); }
 };
 template <>
 struct Ld<float, float> {
@@ -128,7 +131,7 @@ struct Ld<float, float> {
     o[2] = v.z;
     o[3] = v.w;
   }
-  __device__ static float one(const float* p) { return *p; }
+  __device__ static float one(const float* p) { return *gv<float>(p); }
 };
 template <>
 struct Ld<float, double> {
@@ -143,7 +146,7 @@ struct Ld<float, double> {
     o[2] = v.z;
     o[3] = v.w;
   }
-  __device__ static double one(const float* p) { return (double)*p; }
+  __device__ static double one(const float* p) { return (double)*gv<float>(p); }
 };
 template <>
 struct Ld<__hip_bfloat16, float> {
@@ -162,10 +165,10 @@ struct Ld<__hip_bfloat16, float> {
     o[6] = bf_lo(v.w);
     o[7] = bf_hi(v.w);
   }
-  __device__ static float one(const __hip_bfloat16* p) { return __bfloat162float(*p); }
+  __device__ static float one(const __hip_bfloat16* p) { return __uint_as_float((uint32_t)*gv<uint16_t>(p) << 16); }
 };
 
-// VEC consecutive entries of an operand vector (16-byte aligned by construction)
+// VEC consecutive entries of an operand vector
 template <class TC, int VEC>
 __device__ __forceinline__ void ld_b(const TC* p, TC* o) {
   if constexpr (sizeof(TC) == 4) {
@@ -187,14 +190,14 @@ __device__ __forceinline__ void ld_b(const TC* p, TC* o) {
   }
 }
 
-// One wavefront: acc[t] = A[r0 + 16 t + (0..15), 0:ncols] * Bv[0:ncols, 0..15] for t < RT.
+// One wavefront: acc[t] = A[r0 + TS t + (0..15), 0:ncols] * Bv[0:ncols, 0..15] for t < RT.
 // Bv holds column j at Bv + j * ldb (columns >= k read column k - 1; their outputs are
-// not used). Lane l supplies row r0 + 16 t + l % 16 and the reduction slice
+// not used). Lane l supplies row r0 + TS t + l % 16 and the reduction slice
 // [c0 + VEC (l / 16), +VEC) of each step; both operands use the same slice, so the
 // product is exact in any order of the reduction index. Output element e of acc[t]
-// in lane l is row r0 + 16 t + out_row(l / 16, e), column l % 16. Rows past nrows read
+// in lane l is row r0 + TS t + out_row(l / 16, e), column l % 16. Rows past nrows read
 // row nrows - 1 and are not written by the callers.
-template <class TA, class TC, int RT, bool ALN, bool NTL>
+template <class TA, class TC, int RT, bool NTL, int TS = 16>
 __device__ __forceinline__ void mm_rows(const TA* __restrict__ A, int64_t lda, int nrows, int ncols, int r0,
                                         const TC* __restrict__ Bv, int64_t ldb, int k,
                                         typename V4<TC>::t (&acc)[RT]) {
@@ -207,71 +210,74 @@ __device__ __forceinline__ void mm_rows(const TA* __restrict__ A, int64_t lda, i
   const TA* ap[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    const int r = min(r0 + 16 * t + i, nrows - 1);
+    const int r = min(r0 + TS * t + i, nrows - 1);
     ap[t] = A + (int64_t)r * lda + VEC * g;
     acc[t] = typename V4<TC>::t{0, 0, 0, 0};
   }
-  int c0 = 0;
-  if constexpr (ALN) {
-    // trips of UN steps, double-buffered: the loads of trip t + 1 are in flight while
-    // the MFMAs of trip t run
-    constexpr int REGS = RT * VEC * (int)sizeof(TC) / 4;
-    constexpr int UN = REGS >= 32 ? 1 : (REGS >= 16 ? 2 : (REGS >= 8 ? 4 : 8));
-    constexpr int TRIP = UN * STEP;
-    struct Buf {
-      TC a[UN][RT][VEC];
-      TC b[UN][VEC];
-    };
-    auto load = [&](Buf& x, int cb) {
+  // trips of UN steps, double-buffered: the loads of trip t + 1 are in flight while the
+  // MFMAs of trip t run; the steps left over are one more trip, and the elements after the
+  // last step are loaded with it
+  constexpr int REGS = (RT + 1) * VEC * (int)sizeof(TC) / 4;  // of a step; two trips take 64 or 96
+  constexpr int UN = REGS <= 12 ? 4 : 2;
+  static_assert(2 * UN * REGS <= 96, "two trips fit the registers of a wavefront");
+  constexpr int TRIP = UN * STEP;
+  struct Buf {
+    TC a[UN][RT][VEC];
+    TC b[UN][VEC];
+  };
+  auto load_step = [&](Buf& x, int u, int c) {
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
+    for (int t = 0; t < RT; ++t) L::template vec<NTL>(ap[t] + c, x.a[u][t]);
+    ld_b<TC, VEC>(bp + c, x.b[u]);
+  };
+  auto run_step = [&](const Buf& x, int u) {
 #pragma unroll
-        for (int t = 0; t < RT; ++t) L::template vec<NTL>(ap[t] + cb + u * STEP, x.a[u][t]);
-        ld_b<TC, VEC>(bp + cb + u * STEP, x.b[u]);
-      }
-    };
-    auto run = [&](const Buf& x) {
+    for (int m = 0; m < VEC; ++m)
 #pragma unroll
-      for (int u = 0; u < UN; ++u)
+      for (int t = 0; t < RT; ++t) acc[t] = mfma(x.a[u][t][m], x.b[u][m], acc[t]);
+  };
+  auto load = [&](Buf& x, int cb) {
 #pragma unroll
-        for (int m = 0; m < VEC; ++m)
+    for (int u = 0; u < UN; ++u) load_step(x, u, cb + u * STEP);
+  };
+  auto run = [&](const Buf& x) {
 #pragma unroll
-          for (int t = 0; t < RT; ++t) acc[t] = mfma(x.a[u][t][m], x.b[u][m], acc[t]);
-    };
-    const int T = ncols / TRIP;
-    if (T > 0) {
-      Buf x0, x1;
-      load(x0, 0);
-      int t = 0;
-      for (; t + 2 <= T; t += 2) {
-        load(x1, (t + 1) * TRIP);
-        run(x0);
-        if (t + 2 < T) load(x0, (t + 2) * TRIP);
-        run(x1);
-      }
-      if (t < T) run(x0);
-      c0 = T * TRIP;
+    for (int u = 0; u < UN; ++u) run_step(x, u);
+  };
+  const int T = ncols / TRIP;
+  int c0 = T * TRIP;
+  Buf x0;
+  if (T > 0) {
+    Buf x1;
+    load(x0, 0);
+    int t = 0;
+    for (; t + 2 <= T; t += 2) {
+      load(x1, (t + 1) * TRIP);
+      run(x0);
+      if (t + 2 < T) load(x0, (t + 2) * TRIP);
+      run(x1);
     }
-    for (; c0 + STEP <= ncols; c0 += STEP) {
-      TC a[RT][VEC], b[VEC];
-#pragma unroll
-      for (int t = 0; t < RT; ++t) L::template vec<NTL>(ap[t] + c0, a[t]);
-      ld_b<TC, VEC>(bp + c0, b);
-#pragma unroll
-      for (int m = 0; m < VEC; ++m)
-#pragma unroll
-        for (int t = 0; t < RT; ++t) acc[t] = mfma(a[t][m], b[m], acc[t]);
-    }
+    if (t < T) run(x0);
   }
-  for (; c0 < ncols; c0 += STEP) {
-    TC a[RT][VEC], b[VEC];
+  const int left = (ncols - c0) / STEP;  // < UN
+#pragma unroll
+  for (int u = 0; u < UN; ++u)
+    if (u < left) load_step(x0, u, c0 + u * STEP);
+  TC a[RT][VEC], b[VEC];
+  const int ce = c0 + left * STEP;
+  if (ce < ncols) {
 #pragma unroll
     for (int m = 0; m < VEC; ++m) {
-      const bool ok = c0 + VEC * g + m < ncols;
-      b[m] = ok ? bp[c0 + m] : (TC)0;
+      const bool ok = ce + VEC * g + m < ncols;
+      b[m] = ok ? *gv<TC>(bp + ce + m) : (TC)0;
 #pragma unroll
-      for (int t = 0; t < RT; ++t) a[t][m] = ok ? L::one(ap[t] + c0 + m) : (TC)0;
+      for (int t = 0; t < RT; ++t) a[t][m] = ok ? L::one(ap[t] + ce + m) : (TC)0;
     }
+  }
+#pragma unroll
+  for (int u = 0; u < UN; ++u)
+    if (u < left) run_step(x0, u);
+  if (ce < ncols) {
 #pragma unroll
     for (int m = 0; m < VEC; ++m)
 #pragma unroll
@@ -282,13 +288,12 @@ __device__ __forceinline__ void mm_rows(const TA* __restrict__ A, int64_t lda, i
 // Row-tile pass of the workgroup: wavefront w takes row tiles w, w + NW, ... and calls
 // epi(j, row, value) for every output row < nrows and column j < k.
 template <class TA, class TC, int RT, bool NTL, class Epi>
-__device__ __forceinline__ void rows_pass(const TA* A, int64_t lda, int nrows, int ncols, bool aln, const TC* Bv,
-                                          int64_t ldb, int k, Epi epi) {
+__device__ __forceinline__ void rows_pass(const TA* A, int64_t lda, int nrows, int ncols, const TC* Bv, int64_t ldb,
+                                          int k, Epi epi) {
   const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1), i = lane & 15, g = lane >> 4;
   for (int r0 = w * 16 * RT; r0 < nrows; r0 += NW * 16 * RT) {
     typename V4<TC>::t acc[RT];
-    if (aln) mm_rows<TA, TC, RT, true, NTL>(A, lda, nrows, ncols, r0, Bv, ldb, k, acc);
-    else mm_rows<TA, TC, RT, false, NTL>(A, lda, nrows, ncols, r0, Bv, ldb, k, acc);
+    mm_rows<TA, TC, RT, NTL>(A, lda, nrows, ncols, r0, Bv, ldb, k, acc);
     if (i < k) {
 #pragma unroll
       for (int t = 0; t < RT; ++t)
@@ -319,7 +324,6 @@ struct Ctx {
   float* pf;
   Cols *CH, *C1, *C2;
   double lam_lo;  // shift of the low-precision sweeps: lam, plus delta under refinement
-  double* vx;    // LDS: [L2S][KB] block of s-vectors (level2_lds)
   double* part;  // [NW][KB]
   int* shi;      // [8] LDS ints for broadcasts
   int epoch;     // thread 0: last published sweep epoch
@@ -347,9 +351,8 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 
 // true in every thread if some column j < k of C is active (call after a barrier)
 __device__ __forceinline__ bool any_active(const Cols* C, int k) {
-  bool a = false;
-  for (int j = 0; j < k; ++j) a = a || (C->done[j] == 0);
-  return a;
+  const int j = threadIdx.x & (KB - 1);
+  return __any(j < k && C->done[j] == 0);
 }
 
 // ---- one A-sweep as chunked work ---------------------------------------------------
@@ -366,97 +369,103 @@ struct Job {
   double* out;
   double* cpart;
   double lam;
-  int n, ncols, ldn, k, mode, aln;
+  int n, ncols, ldn, k, mode;
 };
 
-template <class TA, class TC>
-__device__ void sweep_chunks(const Job& J, int ch0, int ch1, double* part /*LDS NW*KB*/) {
+// RT adjacent chunks at once (1 or 2): two tiles of a wavefront share the loads of x
+template <class TA, class TC, int RT>
+__device__ void sweep_chunk(const Job& J, int ch, double* part /*LDS NW*KB*/) {
   const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
-  for (int ch = ch0; ch < ch1; ++ch) {
-    const int r0 = ch * CHR + w * 16 * CRT;
-    double pq = 0.0;
-    if (r0 < J.n) {
-      typename V4<TC>::t acc[CRT];
-      if (J.aln)
-        mm_rows<TA, TC, CRT, true, true>((const TA*)J.A, J.lda, J.n, J.ncols, r0, (const TC*)J.Bv, J.ldb, J.k, acc);
-      else
-        mm_rows<TA, TC, CRT, false, true>((const TA*)J.A, J.lda, J.n, J.ncols, r0, (const TC*)J.Bv, J.ldb, J.k, acc);
-      if (i < J.k) {
-#pragma unroll
-        for (int t = 0; t < CRT; ++t)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int row = r0 + 16 * t + out_row<TC>(g, e);
-            if (row < J.n) {
-              const int64_t o = (int64_t)i * J.ldn + row;
-              const double xv = J.x[o];
-              const double q = (double)acc[t][e] + J.lam * xv;
-              if (J.mode == 2) {
-                J.out[o] = J.rhs[(int64_t)i * J.ldr + row] - q;
-              } else {
-                J.out[o] = q;
-                pq = fma(xv, q, pq);
-              }
-            }
-          }
-      }
-    }
-    // the chunk's partial per column: lanes l, l+16, l+32, l+48 hold column l
-    pq += __shfl_xor(pq, 16, WAVE);
-    pq += __shfl_xor(pq, 32, WAVE);
-    if (lane < KB) part[w * KB + lane] = pq;
-    __syncthreads();
-    if (threadIdx.x < (unsigned)J.k) {
-      double t = 0.0;
-      for (int q = 0; q < NW; ++q) t += part[q * KB + threadIdx.x];
-      J.cpart[(int64_t)ch * KB + threadIdx.x] = t;
-    }
-    __syncthreads();
-  }
-}
-
-
-// mode 3: out = (rhs - Y x) * lam on the rows of the chunks (x: s-vectors, ld ldb)
-template <class TY>
-__device__ void yz_chunks(const Job& J, int ch0, int ch1) {
-  const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
-  for (int ch = ch0; ch < ch1; ++ch) {
-    const int r0 = ch * CHR + w * 16 * CRT;
-    if (r0 >= J.n) continue;
-    v4d acc[CRT];
-    if (J.aln)
-      mm_rows<TY, double, CRT, true, false>((const TY*)J.A, J.lda, J.n, J.ncols, r0, (const double*)J.Bv, J.ldb, J.k,
-                                            acc);
-    else
-      mm_rows<TY, double, CRT, false, false>((const TY*)J.A, J.lda, J.n, J.ncols, r0, (const double*)J.Bv, J.ldb, J.k,
-                                             acc);
+  const int r0 = ch * CHR + w * 16;
+  double pq[RT] = {};
+  if (r0 < J.n) {
+    typename V4<TC>::t acc[RT];
+    mm_rows<TA, TC, RT, true, CHR>((const TA*)J.A, J.lda, J.n, J.ncols, r0, (const TC*)J.Bv, J.ldb, J.k, acc);
     if (i < J.k) {
 #pragma unroll
-      for (int t = 0; t < CRT; ++t)
+      for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int row = r0 + 16 * t + out_row<double>(g, e);
+          const int row = r0 + CHR * t + out_row<TC>(g, e);
           if (row < J.n) {
             const int64_t o = (int64_t)i * J.ldn + row;
-            J.out[o] = (J.rhs[(int64_t)i * J.ldr + row] - acc[t][e]) * J.lam;
+            const double xv = *gv<double>(J.x + o);
+            const double q = (double)acc[t][e] + J.lam * xv;
+            if (J.mode == 2) {
+              J.out[o] = *gv<double>(J.rhs + (int64_t)i * J.ldr + row) - q;
+            } else {
+              J.out[o] = q;
+              pq[t] = fma(xv, q, pq[t]);
+            }
           }
         }
     }
   }
+#pragma unroll
+  for (int u = 0; u < RT; ++u) {
+    // a chunk's partial per column: lanes l, l+16, l+32, l+48 hold column l
+    double v = pq[u];
+    v += __shfl_xor(v, 16, WAVE);
+    v += __shfl_xor(v, 32, WAVE);
+    if (lane < KB) part[w * KB + lane] = v;
+    __syncthreads();
+    if (threadIdx.x < (unsigned)J.k) {
+      double t = 0.0;
+      for (int q = 0; q < NW; ++q) t += part[q * KB + threadIdx.x];
+      J.cpart[(int64_t)(ch + u) * KB + threadIdx.x] = t;
+    }
+    __syncthreads();
+  }
+}
+// (the three kinds of chunk work are not inlined: each has the registers for its own loads)
+template <class TA, class TC>
+__device__ __attribute__((noinline)) void sweep_chunks(const Job& J, int ch0, int ch1, double* part) {
+  int ch = ch0;
+  for (; ch + 2 <= ch1; ch += 2) sweep_chunk<TA, TC, 2>(J, ch, part);
+  if (ch < ch1) sweep_chunk<TA, TC, 1>(J, ch, part);
 }
 
-// mode 4: out[ch][j][c] = sum over the rows of chunk ch of Y[row, c] rhs_j[row]; the
-// 16-column tiles of Y are the MFMA rows and the chunk's rows the reduction
+// mode 3: out = (rhs - Y x) * lam on the rows of the chunks (x: s-vectors, ld ldb)
+template <class TY, int RT>
+__device__ void yz_chunk(const Job& J, int ch) {
+  const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
+  const int r0 = ch * CHR + w * 16;
+  if (r0 >= J.n) return;
+  v4d acc[RT];
+  mm_rows<TY, double, RT, false, CHR>((const TY*)J.A, J.lda, J.n, J.ncols, r0, (const double*)J.Bv, J.ldb, J.k, acc);
+  if (i < J.k) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = r0 + CHR * t + out_row<double>(g, e);
+        if (row < J.n) {
+          const int64_t o = (int64_t)i * J.ldn + row;
+          J.out[o] = (*gv<double>(J.rhs + (int64_t)i * J.ldr + row) - acc[t][e]) * J.lam;
+        }
+      }
+  }
+}
 template <class TY>
-__device__ void ytr_chunks(const Job& J, int ch0, int ch1) {
+__device__ __attribute__((noinline)) void yz_chunks(const Job& J, int ch0, int ch1) {
+  int ch = ch0;
+  for (; ch + 2 <= ch1; ch += 2) yz_chunk<TY, 2>(J, ch);
+  if (ch < ch1) yz_chunk<TY, 1>(J, ch);
+}
+
+// mode 4: out[ch][j][c] = sum over the rows of part ch (batch_yt_rows) of Y[row, c] rhs_j[row];
+// the 16-column tiles of Y are the MFMA rows and the part's rows the reduction
+template <class TY>
+__device__ __attribute__((noinline)) void ytr_chunks(const Job& J, int ch0, int ch1) {
   const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
   const int s = J.ncols;
   const int T = (s + 15) / 16;
   const int jb = i < J.k ? i : J.k - 1;
   const TY* Y = (const TY*)J.A;
   const double* V = J.rhs + (int64_t)jb * J.ldr;
+  const int chr = batch_yt_rows(J.n);
   for (int ch = ch0; ch < ch1; ++ch) {
-    const int rb = ch * CHR, re = min(J.n, rb + CHR);
+    const int rb = ch * chr, re = min(J.n, rb + chr);
     for (int tile = w; tile < T; tile += NW) {
       const int c0 = tile * 16;
       const int col = min(c0 + i, s - 1);
@@ -467,8 +476,8 @@ __device__ void ytr_chunks(const Job& J, int ch0, int ch1) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
           const int row = r + 4 * u + g;
-          a[u] = (double)Y[(int64_t)row * J.lda + col];
-          b[u] = V[row];
+          a[u] = (double)*gv<TY>(Y + (int64_t)row * J.lda + col);
+          b[u] = *gv<double>(V + row);
         }
 #pragma unroll
         for (int u = 0; u < 16; ++u) acc = mfma(a[u], b[u], acc);
@@ -479,8 +488,8 @@ __device__ void ytr_chunks(const Job& J, int ch0, int ch1) {
         for (int u = 0; u < 4; ++u) {
           const int row = r + 4 * u + g;
           const bool ok = row < re;
-          a[u] = ok ? (double)Y[(int64_t)row * J.lda + col] : 0.0;
-          b[u] = ok ? V[row] : 0.0;
+          a[u] = ok ? (double)*gv<TY>(Y + (int64_t)row * J.lda + col) : 0.0;
+          b[u] = ok ? *gv<double>(V + row) : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc = mfma(a[u], b[u], acc);
@@ -522,11 +531,17 @@ __device__ __forceinline__ void fence_acq() { __builtin_amdgcn_fence(__ATOMIC_AC
 __device__ __forceinline__ void st_rel(int32_t* p, int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
+// (a claim only decides who; the data is ordered by the epoch and by done)
 __device__ __forceinline__ bool cas_claim(int32_t* p, int e) {
   int cur = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (cur == e) return false;
-  return __hip_atomic_compare_exchange_strong(p, &cur, e, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
+  return __hip_atomic_compare_exchange_strong(p, &cur, e, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
+}
+// parts of a job: row chunks, mode 4 in its own length
+__device__ __forceinline__ int job_parts(int n, int mode) {
+  const int chr = mode == 4 ? batch_yt_rows(n) : CHR;
+  return (n + chr - 1) / chr;
 }
 __device__ __forceinline__ int slice_begin(int s, int nslice, int nch) { return (int)((int64_t)s * nch / nslice); }
 
@@ -534,7 +549,7 @@ __device__ __forceinline__ int slice_begin(int s, int nslice, int nch) { return 
 // slice 0 itself, then every other slice done by a helper or, unclaimed, by itself
 template <class TLO, class THI, class TY>
 __device__ void run_job(Ctx& c, const Job& J) {
-  const int nch = (J.n + CHR - 1) / CHR;
+  const int nch = job_parts(J.n, J.mode);
   BatchTeam* T = c.S.team;
   if (threadIdx.x == 0) {
     int H = 0;
@@ -557,37 +572,52 @@ __device__ void run_job(Ctx& c, const Job& J) {
       st_rel(&T->epoch, c.epoch);  // after the barrier that ended the writes of x
     }
     c.shi[0] = H;
+    c.shi[1] = c.epoch;
   }
   __syncthreads();
   const int H = c.shi[0];
   do_chunks<TLO, THI, TY>(J, 0, slice_begin(1, H + 1, nch), c.part);
-  for (int s = 1; s <= H; ++s) {
-    if (threadIdx.x == 0) {
-      int self = 0;
-      const uint64_t t0 = wall_clock64();
-      while (true) {
-        if (ld_rlx(&T->done[s]) == c.epoch) {
-          fence_acq();
-          c.helped += 1;
-          break;
-        }
-        const uint64_t dt = wall_clock64() - t0;
-        if (dt > CLAIM_TICKS && cas_claim(&T->claim[s], c.epoch)) {
-          self = 1;
-          c.selfdone += 1;
-          break;
-        }
-        if (dt > SLICE_TICKS) {
-          c.team_err = 1;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(2);
+  if (H == 0) return;  // (do_chunks ends with a barrier)
+  // thread s waits for slice s: a flag is a load from beyond the caches, one after the other
+  // would cost its latency for every helper
+  static_assert(MAXH < WAVE, "one wavefront waits");
+  int self = 0, err = 0, got = 0;
+  if (threadIdx.x >= 1 && threadIdx.x <= (unsigned)H) {
+    const int s = threadIdx.x, epoch = c.shi[1];
+    const uint64_t t0 = wall_clock64();
+    while (true) {
+      if (ld_rlx(&T->done[s]) == epoch) {
+        got = 1;
+        break;
       }
-      c.shi[1] = self;
+      const uint64_t dt = wall_clock64() - t0;
+      if (dt > CLAIM_TICKS && cas_claim(&T->claim[s], epoch)) {
+        self = 1;
+        break;
+      }
+      if (dt > SLICE_TICKS) {
+        err = 1;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
     }
-    __syncthreads();
-    if (c.shi[1]) do_chunks<TLO, THI, TY>(J, slice_begin(s, H + 1, nch), slice_begin(s + 1, H + 1, nch), c.part);
   }
+  if (threadIdx.x < WAVE) {
+    fence_acq();
+    const uint64_t ms = __ballot(self);
+    const int ng = __popcll(__ballot(got)), ne = __popcll(__ballot(err));
+    if (threadIdx.x == 0) {
+      c.helped += ng;
+      c.selfdone += __popcll(ms);
+      if (ne) c.team_err = 1;
+      c.shi[2] = (int)(uint32_t)ms;
+    }
+  }
+  __syncthreads();
+  const uint32_t mine = (uint32_t)c.shi[2];  // slices taken back (MAXH = 31: bits 1 to 31)
+  for (int s = 1; s <= H; ++s)
+    if (mine >> s & 1)
+      do_chunks<TLO, THI, TY>(J, slice_begin(s, H + 1, nch), slice_begin(s + 1, H + 1, nch), c.part);
   __syncthreads();
 }
 
@@ -596,7 +626,7 @@ __device__ __forceinline__ void chunk_sum(const Ctx& c, const double* cpart, Col
   const int nch = (c.n + CHR - 1) / CHR;
   if (threadIdx.x < (unsigned)c.k) {
     double t = 0.0;
-    for (int ch = 0; ch < nch; ++ch) t += cpart[(int64_t)ch * KB + threadIdx.x];
+    _Pragma("unroll 8") for (int ch = 0; ch < nch; ++ch) t += *gv<double>(cpart + (int64_t)ch * KB + threadIdx.x);
     C->pq[threadIdx.x] = t;
   }
   __syncthreads();
@@ -609,8 +639,7 @@ struct Batch {
   static __device__ void op_lo(Ctx& c) {
     PhaseTimer tm(c, BT_SWEEP_LO);
     const int w = wave_id(), lane = lane_id();
-    Job J{c.S.A_lo, c.S.lda, c.p1, c.ldn, c.p1, nullptr, 0, c.q1, c.S.cpart, c.lam_lo, c.n, c.n, c.ldn, c.k, 0,
-          c.S.aln_lo};
+    Job J{c.S.A_lo, c.S.lda, c.p1, c.ldn, c.p1, nullptr, 0, c.q1, c.S.cpart, c.lam_lo, c.n, c.n, c.ldn, c.k, 0};
     if constexpr (sizeof(TLO) != 8) {
       if (w < c.k)
         _Pragma("unroll 4") for (int i = lane; i < c.n; i += WAVE) c.pf[(int64_t)w * c.ldn + i] = (float)c.p1[(int64_t)w * c.ldn + i];
@@ -626,7 +655,7 @@ struct Batch {
   static __device__ void op_hi(Ctx& c, int mode, const double* x, const double* rhs, int64_t ldr, double* out) {
     PhaseTimer tm(c, BT_SWEEP_HI);
     const Job J{c.S.A_hi, c.S.lda, x, c.ldn, x, rhs, ldr, out, c.S.cpart, c.S.lam, c.n, c.n, c.ldn, c.k,
-                mode == 0 ? 1 : 2, c.S.aln_hi};
+                mode == 0 ? 1 : 2};
     __syncthreads();
     run_job<TLO, THI, TY>(c, J);
     if (mode == 0) chunk_sum(c, c.S.cpart, c.CH);
@@ -635,32 +664,30 @@ struct Batch {
   // out = M v for an s x s FP64 matrix (row-major, ld s); v, out: s-vectors
   static __device__ void smv(Ctx& c, const double* M, const double* v, double* out) {
     auto epi = [&](int j, int row, double val) { out[(int64_t)j * c.lds + row] = val; };
-    rows_pass<double, double, 1, false>(M, c.s, c.s, c.s, c.S.aln_m, v, c.lds, c.k, epi);
+    rows_pass<double, double, 1, false>(M, c.s, c.s, c.s, v, c.lds, c.k, epi);
     __syncthreads();
   }
 
   // z1 = (r1 - Y y2) / lam~ (written for every column; only active ones are read)
   static __device__ void y_z(Ctx& c) {
     PhaseTimer tm(c, BT_YZ);
-    const Job J{c.S.Y, c.S.ldy, c.y2, c.lds, nullptr, c.r1, c.ldn, c.z1, nullptr, 1.0 / c.S.lt, c.n, c.s, c.ldn, c.k, 3,
-                c.S.aln_y};
+    const Job J{c.S.Y, c.S.ldy, c.y2, c.lds, nullptr, c.r1, c.ldn, c.z1, nullptr, 1.0 / c.S.lt, c.n, c.s, c.ldn, c.k, 3};
     __syncthreads();
     run_job<TLO, THI, TY>(c, J);
   }
 
-  // b2 = Y^T r1 from chunk partials (each 512 rows: 16-column tiles of Y as MFMA rows, the
-  // chunk's rows as the reduction), added in chunk order
+  // b2 = Y^T r1 from the partials of batch_yt_rows rows (16-column tiles of Y as MFMA rows,
+  // the part's rows as the reduction), added in their order
   static __device__ void yt_r(Ctx& c) {
     PhaseTimer tm(c, BT_YT);
-    const Job J{c.S.Y, c.S.ldy, nullptr, 0, nullptr, c.r1, c.ldn, c.S.ypart, nullptr, 0.0, c.n, c.s, c.ldn, c.k, 4,
-                c.S.aln_y};
+    const Job J{c.S.Y, c.S.ldy, nullptr, 0, nullptr, c.r1, c.ldn, c.S.ypart, nullptr, 0.0, c.n, c.s, c.ldn, c.k, 4};
     __syncthreads();
     run_job<TLO, THI, TY>(c, J);
-    const int nch = (c.n + CHR - 1) / CHR;
+    const int nch = job_parts(c.n, 4);
     for (int t = threadIdx.x; t < c.k * c.s; t += NTB) {
-      const int j = t / c.s, cc = t % c.s;
+      const int j = t / c.s, cc = t % c.s;  // element t of every partial
       double v = 0.0;
-      for (int ch = 0; ch < nch; ++ch) v += c.S.ypart[((int64_t)ch * KB + j) * c.s + cc];
+      _Pragma("unroll 8") for (int ch = 0; ch < nch; ++ch) v += *gv<double>(c.S.ypart + (int64_t)ch * KB * c.s + t);
       c.b2[(int64_t)j * c.lds + cc] = v;
     }
     __syncthreads();
@@ -685,155 +712,188 @@ struct Batch {
   }
 
   // ---- the level-2 iteration for s <= L2S ------------------------------------------
-  // Wavefront j keeps all the vectors of column j in registers (element lane + 64 m); the
-  // only traffic of a step is the two s x s operands from L2, one 16-row tile per wavefront, and
-  // the multiplied block and the product through one LDS buffer. The block is stored as
-  // [element][column] with the columns rotated by the element, which keeps both the element-wise
-  // accesses (a wavefront's own column) and the matrix-core operands (16 columns of an element)
-  // off each other's banks. Bound by the FP64 matrix cores of one compute unit (6.8 us per
-  // product at s = 256). s = 256, 16 columns: 103 us per step with the vectors in global memory,
-  // L2STEP us with this.
+  // Wavefront j keeps the vectors of column j in registers (element lane + 64 m); a step's
+  // traffic is the two s x s operands from L2 and, through LDS, the multiplied block and the
+  // product. The block is stored as [element][column] with the columns rotated by the element,
+  // which keeps the element-wise accesses (a wavefront's own column) and the matrix-core
+  // operands (16 columns of an element) off each other's banks.
+  // Product: wavefronts 2 p and 2 p + 1 form rows [32 p, 32 p + 32) from the even and odd
+  // 16-element blocks of the reduction. Both operands are symmetric, so the rows are read as
+  // columns: four whole 256-byte pieces per load, a lane's two elements feeding the tiles of
+  // the even and the odd rows. (Row by row, 16 half lines 8 s bytes apart per load, the loads
+  // met in a few sets of the cache: 30 us per step at s = 256 and 18 at s = 192 but 13.5 at 168.)
+  // Bound by the FP64 matrix cores of one compute unit, 6.85 us per product at s = 256.
+  // s = 256, 16 columns: 103 us per step with the vectors in global memory, 22 us with this.
   static __device__ __forceinline__ int vx_at(int e, int col) { return e * KB + ((col + e) & (KB - 1)); }
 
-  // out = M x (x, out: element lane + 64 m of the wavefront's column); called by all wavefronts
-  static __device__ void smv_lds(Ctx& c, const double* __restrict__ M, const double (&x)[4], double (&out)[4]) {
-    const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
-    const int s = c.s;
+  // 16-byte loads at element alignment (any s >= 2), trips of 16 rows, an even number of them.
+  // Two trips are in flight, over the end of a product too: the first trips of the next one pass
+  // behind the exchange and the reductions. Every path issues the same loads, which is what lets
+  // the compiler wait for the older trip alone.
+  typedef double u2 __attribute__((ext_vector_type(2), aligned(8)));
+  static constexpr int L2U = 4;  // loads of a trip
+  static __device__ __forceinline__ void l2_load(const double* col, int s, int k0, u2 (&d)[L2U]) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) c.vx[vx_at(lane + WAVE * m, w)] = x[m];  // zero beyond s
-    __syncthreads();
-    v4d acc = {0, 0, 0, 0};
-    if (16 * w < s) {  // whole wavefronts
-      // 16-byte loads at element alignment (any s)
-      typedef double u2 __attribute__((ext_vector_type(2), aligned(8)));
-      const double* row = M + (int64_t)min(16 * w + i, s - 1) * s;
-      auto mul = [&](double a0, double a1, int e) {
-        acc = mfma(a0, c.vx[vx_at(e, i)], acc);
-        acc = mfma(a1, c.vx[vx_at(e + 1, i)], acc);
-      };
-      constexpr int U = 8;
-      int c0 = 0;
-      for (; c0 + 8 * U <= s; c0 += 8 * U) {
-        u2 a[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = *gv<u2>(row + c0 + 8 * u + 2 * g);
-#pragma unroll
-        for (int u = 0; u < U; ++u) mul(a[u].x, a[u].y, c0 + 8 * u + 2 * g);
-      }
-      for (; c0 < s; c0 += 8) {  // elements beyond s are zero in LDS; columns stay in the row
-        const int e = c0 + 2 * g;
-        const double a0 = row[min(e, s - 1)], a1 = row[min(e + 1, s - 1)];
-        mul(a0, a1, e);
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c.vx[vx_at(16 * w + out_row<double>(g, e), i)] = acc[e];
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int e = lane + WAVE * m;
-      out[m] = e < s ? c.vx[vx_at(e, w)] : 0.0;
-    }
-    __syncthreads();
+    for (int u = 0; u < L2U; ++u) d[u] = *gv<u2>(col + (int64_t)min(k0 + 4 * u, s - 1) * s);
   }
 
-  static __device__ void level2_lds(Ctx& c) {
+  // y2 = the level-2 solve of b2 for the columns active at level 1 (done1); returns its steps.
+  // Not inlined: the register budget is the loop's alone.
+  static __device__ __attribute__((noinline)) int level2_lds(const double* __restrict__ H,
+                                                             const double* __restrict__ Minv, int s_, int k_, int lds,
+                                                             const double* __restrict__ b2, double* __restrict__ y2,
+                                                             const int* done1, double inner_tol, int max_inner_) {
     using wave_ops::wave_sum;
-    const int w = wave_id(), lane = lane_id();
-    Cols* D = c.C2;
-    double r[4], ro[4], z[4], p[4], q[4], y[4];
-    double bn = 0.0, rz = 0.0;
-    int itj = 0;
-    int dj = 4;
+    __shared__ double vx[L2S * KB], vr[2][L2S * KB];  // declared here: LDS instructions, not flat ones
+    __shared__ double ly[KB][L2S];                    // the iterate, by wavefront
+    __shared__ int done[KB];
+    // (arguments of a call come in vector registers: the loop's bounds go back to scalar ones)
+    const int s = __builtin_amdgcn_readfirstlane(s_), k = __builtin_amdgcn_readfirstlane(k_);
+    const int max_inner = __builtin_amdgcn_readfirstlane(max_inner_);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int lane0 = lane_id();
+    double r[4], ro[4], p[4];
+    double bn, rz = 0.0;
+    int itj = 0, dj;
     {
-      const bool act = w < c.k && c.C1->done[w] == 0;
+      const bool act = w < k && done1[w] == 0;
       double acc = 0.0;
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        const int e = lane + WAVE * m;
-        r[m] = (act && e < c.s) ? c.b2[(int64_t)w * c.lds + e] : 0.0;
-        y[m] = p[m] = 0.0;
+        const int e = lane0 + WAVE * m;
+        r[m] = (act && e < s) ? b2[(int64_t)w * lds + e] : 0.0;
+        p[m] = ro[m] = ly[w][e] = 0.0;
         acc = fma(r[m], r[m], acc);
       }
       bn = sqrt(wave_sum(acc));
       dj = (!act || bn == 0.0) ? 4 : 0;
-      if (lane == 0) D->done[w] = dj;  // (Cols holds KB = NW columns)
-    }
-    const uint64_t l2t0 = (c.P.profile && threadIdx.x == 0) ? wall_clock64() : 0;
-    smv_lds(c, c.S.Minv, r, z);
-    {
-      double acc = 0.0;
+      if (lane0 == 0) done[w] = dj;  // KB = NW columns
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        p[m] = dj == 0 ? z[m] : 0.0;
-        acc = fma(r[m], z[m], acc);
-      }
-      rz = wave_sum(acc);
+      for (int m = 0; m < 4; ++m) vx[vx_at(lane0 + WAVE * m, w)] = r[m];  // zero beyond s
+    }
+    const int r0 = 32 * (w >> 1), h = w & 1;
+    const int T = (s + 63) / 64 * 2;
+    u2 a0[L2U], a1[L2U];
+    {
+      const double* col = Minv + min(r0 + 2 * (lane0 & 15), s - 2);
+      l2_load(col, s, 16 * h + (lane0 >> 4), a0);
+      l2_load(col, s, 16 * h + 32 + (lane0 >> 4), a1);
     }
     int it = 0;
-    while (it < c.P.max_inner) {
+    // one product per trip: Minv r first, then H p and Minv r in turn
+    for (int phase = -1;;) {
+      int lane = lane0;
+      asm volatile("" : "+v"(lane));  // the addresses are formed in the loop, not kept (they would spill)
+      const int i = lane & 15, g = lane >> 4;
       __syncthreads();
-      if (!any_active(D, NW)) break;
-      smv_lds(c, c.S.H, p, q);
-      if (dj == 0) {
-        double pq = 0.0;
+      if (!__any(done[i] == 0)) break;
+      if (r0 < s) {  // whole wavefronts
+        const double* const M = phase == 1 ? H : Minv;
+        const double* const Mn = phase == 1 ? Minv : H;
+        const int c0 = r0 + 2 * i, cl = min(c0, s - 2);
+        const bool sh = c0 == s - 1;  // an odd last row: loaded from s - 2
+        v4d e0 = {0, 0, 0, 0}, e1 = {0, 0, 0, 0};
+        auto use = [&](const u2(&d)[L2U], int k0) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) pq = fma(p[m], q[m], pq);
-        pq = wave_sum(pq);
-        const bool brk = !(pq > 0.0);
-        const double al = brk ? 0.0 : rz / pq;
-        double acc = 0.0;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          y[m] = fma(al, p[m], y[m]);
-          ro[m] = r[m];
-          r[m] = fma(-al, q[m], r[m]);
-          acc = fma(r[m], r[m], acc);
+          for (int u = 0; u < L2U; ++u) {
+            const double b = vx[vx_at(k0 + 4 * u + g, i)];  // zero beyond s
+            e0 = mfma(sh ? d[u].y : d[u].x, b, e0);
+            e1 = mfma(d[u].y, b, e1);
+          }
+        };
+        for (int t = 0; t < T; t += 2) {
+          const bool last = t + 2 >= T;
+          const double* const src = (last ? Mn : M) + cl;
+          const int k0 = 16 * (2 * t + h), kn = last ? 16 * h : k0 + 64;
+          if (k0 < s) use(a0, k0);
+          l2_load(src, s, kn + g, a0);
+          if (k0 + 32 < s) use(a1, k0 + 32);
+          l2_load(src, s, kn + 32 + g, a1);
         }
-        const double rn = sqrt(wave_sum(acc));
-        ++itj;
-        if (brk || !(rn == rn)) dj = 2;
-        else if (rn <= c.P.inner_tol * bn) dj = 1;
-        else if (itj >= c.P.max_inner) dj = 3;
-        if (lane == 0) D->done[w] = dj;
-      }
-      ++it;
-      __syncthreads();
-      if (!any_active(D, NW)) break;
-      smv_lds(c, c.S.Minv, r, z);
-      if (dj == 0) {
-        double zr = 0.0, zro = 0.0;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          zr = fma(z[m], r[m], zr);
-          zro = fma(z[m], ro[m], zro);
-        }
-        zr = wave_sum(zr);
-        zro = wave_sum(zro);
-        if (rz != 0.0 && isfinite(rz)) {
-          const double beta = (zr - zro) / rz;
-#pragma unroll
-          for (int m = 0; m < 4; ++m) p[m] = fma(beta, p[m], z[m]);
-          rz = zr;
-        } else {
-          dj = 2;  // beta's denominator vanished: breakdown, the iterate is kept
-          if (lane == 0) D->done[w] = dj;
+        for (int e = 0; e < 4; ++e) {
+          const int row = r0 + 2 * out_row<double>(g, e);
+          vr[h][vx_at(row, i)] = e0[e];
+          vr[h][vx_at(row + 1, i)] = e1[e];
         }
       }
-    }
-    if (w < c.k) {
+      __syncthreads();
+      // from here to the next barrier a wavefront touches its own column alone
+      double o[4];
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         const int e = lane + WAVE * m;
-        if (e < c.s) c.y2[(int64_t)w * c.lds + e] = y[m];
+        o[m] = e < s ? vr[0][vx_at(e, w)] + vr[1][vx_at(e, w)] : 0.0;
+      }
+      if (phase == 1) {  // o = H p
+        if (dj == 0) {
+          double pq = 0.0;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) pq = fma(p[m], o[m], pq);
+          pq = wave_sum(pq);
+          const bool brk = !(pq > 0.0);
+          const double al = brk ? 0.0 : rz / pq;
+          double rr = 0.0;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            const int e = lane + WAVE * m;
+            ly[w][e] = fma(al, p[m], ly[w][e]);
+            ro[m] = r[m];
+            r[m] = fma(-al, o[m], r[m]);
+            rr = fma(r[m], r[m], rr);
+          }
+          const double rn = sqrt(wave_sum(rr));
+          ++itj;
+          if (brk || !(rn == rn)) dj = 2;
+          else if (rn <= inner_tol * bn) dj = 1;
+          else if (itj >= max_inner) dj = 3;
+          if (lane == 0) done[w] = dj;
+        }
+        ++it;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) vx[vx_at(lane + WAVE * m, w)] = r[m];
+        phase = 0;
+      } else {  // o = Minv r
+        if (dj == 0) {
+          double zr = 0.0, zro = 0.0;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            zr = fma(o[m], r[m], zr);
+            zro = fma(o[m], ro[m], zro);
+          }
+          zr = wave_sum(zr);
+          if (phase < 0) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) p[m] = o[m];
+            rz = zr;
+          } else {
+            zro = wave_sum(zro);
+            if (rz != 0.0 && isfinite(rz)) {
+              const double beta = (zr - zro) / rz;
+#pragma unroll
+              for (int m = 0; m < 4; ++m) p[m] = fma(beta, p[m], o[m]);
+              rz = zr;
+            } else {
+              dj = 2;  // beta's denominator vanished: breakdown, the iterate is kept
+              if (lane == 0) done[w] = dj;
+            }
+          }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) vx[vx_at(lane + WAVE * m, w)] = p[m];
+        phase = 1;
+      }
+      if (phase == 1 && it >= max_inner) break;
+    }
+    if (w < k) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int e = lane0 + WAVE * m;
+        if (e < s) y2[(int64_t)w * lds + e] = ly[w][e];
       }
     }
-    if (threadIdx.x == 0) {
-      c.inner += it;
-      if (c.P.profile) c.ticks[BT_LEVEL2] += wall_clock64() - l2t0;
-    }
     __syncthreads();
+    return it;
   }
 
   // ---- Algorithm 2: z1 = SolveM1(r1) for the columns active at level 1 -------------
@@ -841,8 +901,13 @@ struct Batch {
     const int w = wave_id(), lane = lane_id();
     Cols* D = c.C2;
     yt_r(c);
-    if (c.s <= L2S) {
-      level2_lds(c);
+    if (c.s >= 2 && c.s <= L2S) {
+      const uint64_t t0 = (c.P.profile && threadIdx.x == 0) ? wall_clock64() : 0;
+      const int it = level2_lds(c.S.H, c.S.Minv, c.s, c.k, c.lds, c.b2, c.y2, c.C1->done, c.P.inner_tol, c.P.max_inner);
+      if (threadIdx.x == 0) {
+        c.inner += it;
+        if (c.P.profile) c.ticks[BT_LEVEL2] += wall_clock64() - t0;
+      }
       y_z(c);
       return;
     }
@@ -1246,7 +1311,6 @@ struct JobSh {  // the claimed job, broadcast through LDS
 template <class TLO, class THI, class TY>
 __device__ void serve(const BatchSys& S, int h, int k, double* part, JobSh* js) {
   BatchTeam* T = S.team;
-  const int nch = (S.n + CHR - 1) / CHR;
   int last = 0;
   if (threadIdx.x == 0) last = ld_acq(&T->epoch);  // epochs published before joining are not ours
   while (true) {
@@ -1290,8 +1354,8 @@ __device__ void serve(const BatchSys& S, int h, int k, double* part, JobSh* js) 
       const bool yjob = mode >= 3;
       const Job J{mode == 0 ? S.A_lo : (yjob ? S.Y : S.A_hi),
                   yjob ? S.ldy : S.lda,
-                  js->bv, js->ldb, js->x, js->rhs, js->ldr, js->out, S.cpart, js->lam, S.n, js->ncols, S.ldn, k, mode,
-                  mode == 0 ? S.aln_lo : (yjob ? S.aln_y : S.aln_hi)};
+                  js->bv, js->ldb, js->x, js->rhs, js->ldr, js->out, S.cpart, js->lam, S.n, js->ncols, S.ldn, k, mode};
+      const int nch = job_parts(S.n, mode);
       do_chunks<TLO, THI, TY>(J, slice_begin(h, ns, nch), slice_begin(h + 1, ns, nch), part);
       if (threadIdx.x == 0) st_rel(&T->done[h], js->epoch);  // after the barrier that ended the slice
     }
@@ -1300,20 +1364,25 @@ __device__ void serve(const BatchSys& S, int h, int k, double* part, JobSh* js) 
 }
 
 // pick the unfinished system with the most work per helper and serve it; leave when no
-// system needs help or when some system has not started (its workgroup is waiting for a
-// compute unit: this one is better given back)
+// system needs help or when some system has not started within START_TICKS (its workgroup
+// is waiting for a compute unit: this one is better given back)
 template <class TLO, class THI, class TY>
 __device__ void help(const BatchSys* __restrict__ sys, const BatchPrm& prm, int k, double* part, int* shi,
                      JobSh* js) {
+  const uint64_t t0 = wall_clock64();
   for (int round = 0; round < 4 * MAXH; ++round) {
     if (threadIdx.x == 0) {
       int target = -1, h = 0;
       double best = 0.0;
       for (int j = 0; j < prm.nsys; ++j) {
         BatchTeam* T = sys[j].team;
-        if (!__hip_atomic_load(&T->started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        bool up = ld_rlx(&T->started);
+        while (!up && wall_clock64() - t0 < START_TICKS) {
+          __builtin_amdgcn_s_sleep(8);
+          up = ld_rlx(&T->started);
+        }
+        if (!up) {
           target = -1;
-          best = -1.0;
           break;
         }
         if (__hip_atomic_load(&T->finish, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) continue;
@@ -1328,7 +1397,10 @@ __device__ void help(const BatchSys* __restrict__ sys, const BatchPrm& prm, int 
       }
       if (target >= 0) {
         h = __hip_atomic_fetch_add(&sys[target].team->joined, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
-        if (h > MAXH) target = -2;
+        if (h > min(MAXH, (sys[target].n + CHR - 1) / CHR - 1)) {  // others were faster
+          __hip_atomic_fetch_sub(&sys[target].team->joined, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          target = -2;
+        }
       }
       shi[2] = target;
       shi[3] = h;
@@ -1346,10 +1418,13 @@ template <class TLO, class THI, class TY>
 __global__ void __launch_bounds__(NTB) k_batch_psd(const BatchSys* __restrict__ sys, BatchPrm prm, int k,
                                                    BatchOut* __restrict__ out) {
   __shared__ Cols cH, c1, c2;
-  __shared__ double vx[L2S * KB];
   __shared__ double part[NW * KB];
   __shared__ int shi[8];
   __shared__ JobSh js;
+  if ((int)blockIdx.x >= prm.nsys) {
+    help<TLO, THI, TY>(sys, prm, k, part, shi, &js);
+    return;
+  }
   Ctx c;
   c.S = sys[blockIdx.x];
   c.shi = shi;
@@ -1390,7 +1465,6 @@ __global__ void __launch_bounds__(NTB) k_batch_psd(const BatchSys* __restrict__ 
   c.CH = &cH;
   c.C1 = &c1;
   c.C2 = &c2;
-  c.vx = vx;
   c.part = part;
   c.outer = c.inner = c.refine = c.restarts = 0;
   for (int q = 0; q < BT_NPHASE; ++q) c.ticks[q] = 0;
@@ -1446,7 +1520,8 @@ __global__ void __launch_bounds__(NTB) k_batch_psd(const BatchSys* __restrict__ 
 
 template <class TLO, class THI, class TY>
 hipError_t launch_t(hipStream_t st, const BatchSys* sys, int nsys, const BatchPrm& prm, int k, BatchOut* out) {
-  hipLaunchKernelGGL((k_batch_psd<TLO, THI, TY>), dim3((unsigned)nsys), dim3(NTB), 0, st, sys, prm, k, out);
+  hipLaunchKernelGGL((k_batch_psd<TLO, THI, TY>), dim3((unsigned)(nsys + prm.helpers)), dim3(NTB), 0, st, sys, prm,
+                     k, out);
   return hipGetLastError();
 }
 

@@ -62,8 +62,9 @@ size_t batch_layout(WsCarver& w, int32_t nsys, const msp_system* sys, int kcap, 
     const int64_t n = P->n, s = P->s;
     double* H = w.take<double>(s * s);
     const size_t nch = (size_t)((n + MSP_BATCH_CHR - 1) / MSP_BATCH_CHR);
+    const size_t nyt = (size_t)((n + batch_yt_rows(n) - 1) / batch_yt_rows(n));
     double* cp = w.take<double>(nch * MSP_BATCH_KMAX);
-    double* yp = w.take<double>(nch * MSP_BATCH_KMAX * s);
+    double* yp = w.take<double>(nyt * MSP_BATCH_KMAX * s);
     double* v = w.take<double>((size_t)kcap * (11 * round8(n) + 7 * round8(s)));
     float* f = w.take<float>((size_t)kcap * round8(n));
     if (L) {
@@ -169,6 +170,16 @@ extern "C" msp_status msp_solve_batched(void* stream, int32_t nsys, const msp_sy
   prm.profile = o->profile ? 1 : 0;
   prm.teams = o->batch_teams ? 1 : 0;
   prm.nsys = nsys;
+  if (prm.teams) {
+    // one workgroup fills a compute unit; as many helpers as the systems can use
+    int dev = 0, cus = 0;
+    MSP_CHECK_HIP(hipGetDevice(&dev));
+    MSP_CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    int64_t want = 0;
+    for (int32_t i = 0; i < nsys; ++i)
+      want += std::min<int64_t>((sys[i].P->n + MSP_BATCH_CHR - 1) / MSP_BATCH_CHR - 1, MSP_BATCH_MAXH);
+    prm.helpers = (int32_t)std::max<int64_t>(0, std::min<int64_t>(want, cus - nsys));
+  }
   int clock_khz = 0;
   if (prm.profile) {
     int dev = 0;
@@ -206,10 +217,6 @@ extern "C" msp_status msp_solve_batched(void* stream, int32_t nsys, const msp_sy
       d.lds = (int32_t)round8(P->s);
       d.lam = P->lam;
       d.lt = P->lt;
-      d.aln_lo = aligned16(u.A_lo, u.lda, esize(lo_t));
-      d.aln_hi = aligned16(u.A_hi, u.lda, esize(hi_t));
-      d.aln_y = aligned16(P->Y, P->ldy, esize(yt));
-      d.aln_m = aligned16(P->Minv, P->s, 8) && aligned16(L.H[i], P->s, 8);
       d.team = L.team + q;  // records in launch order: helpers scan the largest systems first
       d.cpart = L.cpart[i];
       d.ypart = L.ypart[i];

@@ -4,11 +4,12 @@
 
 #define MSP_BATCH_KMAX 16  // right-hand sides per launch (the N dimension of the 16x16 tiles)
 #define MSP_BATCH_MAXH 31  // helper workgroups per system
-#define MSP_BATCH_CHR 512  // rows per sweep chunk (16 wavefronts x 32-row tiles)
+#define MSP_BATCH_CHR 256  // rows per chunk (16 wavefronts x 16-row tiles)
 
 // Cooperation record of one system (device memory, zeroed before the launch). The
 // system's own workgroup (the leader) publishes each A-sweep as an epoch; workgroups
-// whose systems are finished join as helpers and claim slices of its row chunks.
+// without a system of their own, or whose systems are finished, join as helpers and claim
+// slices of its row chunks.
 struct BatchTeam {
   int32_t epoch, nslice, mode, finish;
   int32_t joined, started, ncols, pad;
@@ -41,21 +42,25 @@ struct BatchSys {
   float* pf;          // F32 copy of the level-1 direction, kcap x ldn
   int32_t n, s, ldn, lds;
   double lam, lt;     // lambda and lambda~ = lambda + lambda0
-  int32_t aln_lo, aln_hi, aln_y, aln_m;  // rows of A_lo / A_hi / Y / the s x s matrices are 16-byte aligned
   BatchTeam* team;    // cooperation record
   double* cpart;      // per-chunk partials of <x, A x>: [ceil(n / MSP_BATCH_CHR)][MSP_BATCH_KMAX]
-  double* ypart;      // per-chunk partials of Y^T r: [ceil(n / MSP_BATCH_CHR)][MSP_BATCH_KMAX][s]
+  double* ypart;      // partials of Y^T r: [ceil(n / batch_yt_rows(n))][MSP_BATCH_KMAX][s]
   int32_t id;         // position in the caller's array
   int32_t pad;
 };
+
+// Rows per partial of Y^T r: a chunk, and four for long systems, whose leader would otherwise
+// read more partials than it saves.
+inline constexpr int batch_yt_rows(int64_t n) { return n > 8192 ? 4 * MSP_BATCH_CHR : MSP_BATCH_CHR; }
 
 struct BatchPrm {
   double tol, inner_tol, refine_tol;
   int32_t max_outer, max_inner, max_refine, refine;
   int32_t kcap;       // columns allocated per vector
   int32_t profile;    // record wall-clock time per phase (BatchOut.ticks)
-  int32_t teams;      // finished workgroups help the remaining systems' sweeps
+  int32_t teams;      // workgroups without an unfinished system help the remaining systems' sweeps
   int32_t nsys;       // systems in the launch (helpers scan their records)
+  int32_t helpers;    // workgroups launched beyond the systems, as helpers from the start
 };
 
 enum { BT_SWEEP_LO = 0, BT_SWEEP_HI, BT_YT, BT_LEVEL2, BT_YZ, BT_TOTAL, BT_NPHASE };
