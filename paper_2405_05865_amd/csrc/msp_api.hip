@@ -544,13 +544,18 @@ struct SolveCtx {
   size_t evused = 0;
 };
 
-// the one-launch inner solve against the per-step kernels: a launch's steps cost 1.3 to 12 us
-// however many groups it holds (k_pcg.hip), the per-step kernels 6 to 12 us (PSD) or 10 to 36
-// us (general) for up to 16 columns and about 42 us beyond, so a solve may take some launches
-// one after the other
-bool pcg_wins(int64_t s, int64_t k) {
+// The one-launch inner solve against the per-step kernels. A launch's step costs 1.3 to 12 us
+// (k_pcg.hip) and a solve may take some launches one after the other. Up to 16 columns the
+// PSD step kernel costs 6 to 12 us for all of them, which one launch beats and two do not
+// (whole solves at n = 6000, one launch against the step kernel: s = 512, k = 16 99 against
+// 161 ms, s = 700, k = 2 84 against 91; two launches: s = 520, k = 3 141 against 102); the
+// general level 3 costs 10 to 36 us per step (n = 3000, s = 700: k = 2, one launch, 12.6 against
+// 25.5 ms, k = 4, two, 22.6 against 30.0, k = 8, four, 42.0 against 36.9). Beyond 16 columns a
+// step costs 42 us (s = 512, k = 24, two launches: 156 against 344 ms; s = 375, k = 64, four
+// launches: 71 against 108, k = 128, seven: 121 against 110).
+bool pcg_wins(int64_t s, int64_t k, bool psd) {
   const PcgShape h = pcg_shape(s, k);
-  return h.cpl > 0 && h.launches <= (k <= kL2xMaxK ? 4 : 8);
+  return h.cpl > 0 && h.launches <= (k > kL2xMaxK ? 4 : (psd ? 1 : 2));
 }
 
 size_t solve_layout(WsCarver& w, const msp_precond* P, int64_t k, SolveCtx* c, int form, int sym, int l3k) {
@@ -611,7 +616,7 @@ size_t solve_layout(WsCarver& w, const msp_precond* P, int64_t k, SolveCtx* c, i
   const bool use_x = form == 1 && psd && s >= kGemmMinK && s <= kL2xMaxS && k <= kL2xMaxK;
   // whole inner solves in one launch: the PSD level 2 by the same recurrence, the general
   // level 3 by direct products
-  const bool use_p = form == 1 && s >= kGemmMinK && (psd || l3k == 2) && pcg_wins(s, k);
+  const bool use_p = form == 1 && s >= kGemmMinK && (psd || l3k == 2) && pcg_wins(s, k, psd);
   PcgRun pcg{};
   if (use_p) pcg = pcg_carve(w, s, k);
   L2xArgs X{};
