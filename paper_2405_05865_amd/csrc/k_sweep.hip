@@ -277,8 +277,10 @@ __global__ void k_sum_tiles(const double* __restrict__ part, int tiles, int64_t 
 
 // matrices that the memory-side cache holds between sweeps are loaded through the caches,
 // larger ones past them. us per sweep, cached / streamed, FP64: n = 2048 4.9 / 6.9, 6000 43 / 45,
-// 8192 93 / 82, 32768 1425 / 1245.
-bool past_caches(int64_t rows, int64_t cols, int64_t es) { return rows * cols * es > (int64_t(384) << 20); }
+// 8192 93 / 82, 32768 1425 / 1245. The line: whole solves with 3 columns, ms, at 265 MB (FP64,
+// n = 5900) 64.4 / 65.6, at 293 MB 76.6 / 76.0, at 373 MB 91.9 / 86.7; F32 at 262 MB 136 / 137,
+// at 295 MB 152 / 148, at 381 MB 193 / 180 (cached, the sweep also drops what lies between sweeps).
+bool past_caches(int64_t rows, int64_t cols, int64_t es) { return rows * cols * es > (int64_t(280) << 20); }
 
 template <class TA, class TC, int VEC, int R, int K, int UNR = 1>
 hipError_t gemv_t(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X,

@@ -263,10 +263,14 @@ hipError_t symv_t(hipStream_t st, const TA* A, int64_t n, int64_t lda, const dou
 // extra partials stay in the caches. us per sweep with edge 256 / 128 / 64: FP64 n = 1024 20.6 /
 // 10.2 / 6.7, 4096 28 / 19 / 16, 8192 56 / 48 / 47, 16384 189 / 185 / 200; F32 n = 12000 65 / 59 /
 // 68, 32768 387 / 440 / 504. Up to about the size of the memory-side cache the loads go through
-// the caches (n = 8192 with edge 128: 48 us, 50 us past them; n = 16384: 202 us, 185 us).
+// the caches (n = 8192 with edge 128: 48 us, 50 us past them; n = 16384: 202 us, 185 us). The
+// lines between: whole solves, ms, edge 128 cached / edge 128 past the caches / edge 256 past
+// them, at 218 MB 117 / 121 / 121, 262 MB 78.8 / 78.3 / 83.0, 288 MB 88.0 / 84.9 / 88.4, 322 MB
+// 96.9 / 89.3 / 89.2, 332 MB (F32) 162 / 158 / 152, 373 MB (F32) 178 / 173 / 165.
 // (Before, with edge 256 and the row sums exchanged through LDS: 22.9 us at n = 1024, 70 us for
 // F32 n = 12000.) A BF16 row chunk needs an edge of 128.
-constexpr int64_t kTile64Bytes = int64_t(80) << 20, kTile128Bytes = int64_t(400) << 20;
+constexpr int64_t kTile64Bytes = int64_t(80) << 20, kTile128Bytes = int64_t(300) << 20;
+constexpr int64_t kCachedBytes = int64_t(250) << 20;
 int symv_tile(int64_t n, int64_t es) {
   const int64_t bytes = n * n / 2 * es;
   return bytes <= kTile64Bytes && es > 2 ? 64 : (bytes <= kTile128Bytes ? 128 : 256);
@@ -278,7 +282,11 @@ hipError_t symv_d(hipStream_t st, const TA* A, int64_t n, int64_t lda, const dou
   const int T = symv_tile(n, sizeof(TA));
   if constexpr (sizeof(TA) > 2)
     if (T == 64) return symv_t<TA, TC, 64, false>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
-  if (T == 128) return symv_t<TA, TC, 128, false>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
+  if (T == 128) {
+    if (n * n / 2 * (int64_t)sizeof(TA) <= kCachedBytes)
+      return symv_t<TA, TC, 128, false>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
+    return symv_t<TA, TC, 128, true>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
+  }
   return symv_t<TA, TC, 256, true>(st, A, n, lda, x, y, lam, diag, skip, part, dot_part, nblocks);
 }
 
