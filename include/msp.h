@@ -242,8 +242,9 @@ typedef struct {
                               replayed on the solve's stream. Same kernels and results as the
                               eager launches. Inner solves that run as one launch (s <= 1024)
                               have no steps to replay. Default 0. */
-  int32_t batch_teams;     /* msp_solve_batched: a workgroup whose system is finished helps the
-                              A-sweeps of a larger unfinished system (same results bit for bit;
+  int32_t batch_teams;     /* msp_solve_batched: a workgroup whose system is finished, and further
+                              ones where the systems leave compute units free, help the passes
+                              over A and Y of unfinished systems (same results bit for bit;
                               chunked partials in a fixed order). Default 1. */
   int32_t autotune;        /* k >= 8 (level-1 sweeps on the matrix cores): before the first step,
                               time every admissible count of reduction segments (1..64) of the
