@@ -23,11 +23,7 @@ bool batch_log_on() {
   return e && e[0] && e[0] != '0';
 }
 
-size_t esize(msp_dtype t) { return t == MSP_F64 ? 8 : (t == MSP_F32 ? 4 : 2); }
 int64_t round8(int64_t v) { return (v + 7) / 8 * 8; }
-bool aligned16(const void* p, int64_t ld, size_t es) {
-  return ((uintptr_t)p % 16 == 0) && ((ld * (int64_t)es) % 16 == 0);
-}
 
 struct BatchLayout {
   BatchSys* dsys = nullptr;
