@@ -30,6 +30,7 @@
 // by wall-clock time: a slice that no helper claims in time is taken by the leader, and an
 // idle helper leaves.
 #include "msp_batched.h"
+#include "team_claim.h"
 #include "wave_ops.h"
 
 #include <hip/hip_bf16.h>
@@ -538,23 +539,26 @@ __device__ void do_chunks(const Job& J, int ch0, int ch1, double* part) {
   }
 }
 
-__device__ __forceinline__ int ld_acq(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
 // polling without cache maintenance; acquire once the awaited value is seen
-__device__ __forceinline__ int ld_rlx(const int32_t* p) {
+template <class T>
+__device__ __forceinline__ T ld_rlx(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void fence_acq() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
-__device__ __forceinline__ void st_rel(int32_t* p, int v) {
+template <class T>
+__device__ __forceinline__ void st_rel(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
-// (a claim only decides who; the data is ordered by the epoch and by done)
-__device__ __forceinline__ bool cas_claim(int32_t* p, int e) {
-  int cur = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (cur == e) return false;
-  return __hip_atomic_compare_exchange_strong(p, &cur, e, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT);
+// slice for job e (team_claim.h). What the caller has read of the job is complete before: the
+// fence waits for its loads. The data is ordered by the job word and by done.
+__device__ __forceinline__ bool claim_slice(int32_t* p, int e) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  return team::claim(
+      e, [=] { return ld_rlx(p); },
+      [=](int& cur, int to) {
+        return __hip_atomic_compare_exchange_strong(p, &cur, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+      });
 }
 // parts of a job: row chunks, mode 4 in its own length
 __device__ __forceinline__ int job_parts(int n, int mode) {
@@ -585,9 +589,8 @@ __device__ void run_job(Ctx& c, const Job& J) {
       T->ldr = J.ldr;
       T->lam = J.lam;
       T->mode = J.mode;
-      T->nslice = H + 1;
       c.epoch += 1;
-      st_rel(&T->epoch, c.epoch);  // after the barrier that ended the writes of x
+      st_rel(&T->job, team::job_word(c.epoch, H + 1));  // after the barrier that ended the writes of x
     }
     c.shi[0] = H;
     c.shi[1] = c.epoch;
@@ -609,7 +612,7 @@ __device__ void run_job(Ctx& c, const Job& J) {
         break;
       }
       const uint64_t dt = wall_clock64() - t0;
-      if (dt > CLAIM_TICKS && cas_claim(&T->claim[s], epoch)) {
+      if (dt > CLAIM_TICKS && claim_slice(&T->claim[s], epoch)) {
         self = 1;
         break;
       }
@@ -1330,15 +1333,19 @@ template <class TLO, class THI, class TY>
 __device__ void serve(const BatchSys& S, int h, int k, double* part, JobSh* js) {
   BatchTeam* T = S.team;
   int last = 0;
-  if (threadIdx.x == 0) last = ld_acq(&T->epoch);  // epochs published before joining are not ours
+  if (threadIdx.x == 0) last = team::job_epoch(ld_rlx(&T->job));  // jobs published before joining are not ours
   while (true) {
     if (threadIdx.x == 0) {
       int state = 0;  // 0 leave, 1 work, 2 nothing for this helper in this epoch
       const uint64_t t0 = wall_clock64();
       while (true) {
         if (ld_rlx(&T->finish)) break;
-        const int e = ld_rlx(&T->epoch);
+        const int64_t word = ld_rlx(&T->job);
+        const int e = team::job_epoch(word);
         if (e != last) {
+          last = e;
+          state = 2;
+          if (h >= team::job_slices(word)) break;
           fence_acq();
           js->bv = T->bv;
           js->x = T->x;
@@ -1349,11 +1356,9 @@ __device__ void serve(const BatchSys& S, int h, int k, double* part, JobSh* js) 
           js->lam = T->lam;
           js->mode = T->mode;
           js->ncols = T->ncols;
-          js->nslice = T->nslice;
-          if (ld_acq(&T->epoch) != e) continue;  // republished while reading: read again
-          last = e;
+          js->nslice = team::job_slices(word);
           js->epoch = e;
-          state = (h < js->nslice && cas_claim(&T->claim[h], e)) ? 1 : 2;
+          if (claim_slice(&T->claim[h], e)) state = 1;  // (otherwise the leader was faster)
           break;
         }
         if (wall_clock64() - t0 > IDLE_TICKS) break;

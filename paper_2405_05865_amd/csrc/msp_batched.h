@@ -11,9 +11,10 @@
 // without a system of their own, or whose systems are finished, join as helpers and claim
 // slices of its row chunks.
 struct BatchTeam {
-  int32_t epoch, nslice, mode, finish;
+  int64_t job;  // epoch and number of slices of the published job (team_claim.h)
+  int32_t mode, finish;
   int32_t joined, started, ncols, pad;
-  int32_t claim[MSP_BATCH_MAXH + 1];  // slice s claimed for epoch claim[s]
+  int32_t claim[MSP_BATCH_MAXH + 1];  // slice s last claimed for epoch claim[s]
   int32_t done[MSP_BATCH_MAXH + 1];   // slice s completed for epoch done[s]
   // the published job: 0 q = (A_lo + lam I) x, 1 q = (A_hi + lam I) x, 2 out = rhs - (A_hi +
   // lam I) x, 3 out = (rhs - Y x) lam (x s-vectors), 4 chunk partials of Y^T rhs
