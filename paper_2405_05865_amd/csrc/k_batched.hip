@@ -858,9 +858,11 @@ struct Batch {
 #pragma unroll
           for (int m = 0; m < 4; ++m) {
             const int e = lane + WAVE * m;
-            ly[w][e] = fma(al, p[m], ly[w][e]);
             ro[m] = r[m];
-            r[m] = fma(-al, o[m], r[m]);
+            if (!brk) {  // (uniform; a breakdown keeps the iterate, p need not be finite)
+              ly[w][e] = fma(al, p[m], ly[w][e]);
+              r[m] = fma(-al, o[m], r[m]);
+            }
             rr = fma(r[m], r[m], rr);
           }
           const double rn = sqrt(wave_sum(rr));

@@ -375,7 +375,8 @@ struct ShortGroup {
 
 // One launch for q += c t (t may be null), alpha = rz / <p, q>, x += alpha p, r_old = r,
 // r -= alpha q and the decision on |r|. s = 512, 8 columns: the axpby, k_alpha_dot, k_update
-// and k_decide took 24 us, this 8.8 us.
+// and k_decide took 24 us, this 8.8 us. A column that breaks down (<p, q> not positive) keeps x
+// and r untouched: p need not be finite, and x + 0 p would not be x.
 __global__ void __launch_bounds__(NTD) k_short_step(FcgState S, int len, double* __restrict__ x, double* __restrict__ r,
                                                    double* __restrict__ r_old, const double* __restrict__ p,
                                                    double* __restrict__ q, double c, const double* __restrict__ t,
@@ -412,7 +413,7 @@ __global__ void __launch_bounds__(NTD) k_short_step(FcgState S, int len, double*
     const bool brk = !(pq > 0.0);
     const double a = (brk || !live) ? 0.0 : S.rz[j] / pq;
     double rr = 0.0;
-    for (int i0 = 0; live && i0 < len; i0 += U * step) {
+    for (int i0 = 0; live && !brk && i0 < len; i0 += U * step) {
       if (len > U * step) {  // otherwise the values are still in registers
 #pragma unroll
         for (int u = 0; u < U; ++u) {

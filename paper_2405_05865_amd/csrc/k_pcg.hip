@@ -383,8 +383,8 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         publish(1, alpha, dj);
 #pragma unroll
         for (int q = 0; q < EPT; ++q) {
-          if (!col_done(q, dj)) {
-            const double aq = scalar(1, q, alpha);
+          const double aq = scalar(1, q, alpha);
+          if (!col_done(q, dj) && aq != 0.0) {  // 0: a breakdown keeps the iterate, p need not be finite
             r[q] = fma(-aq, u[q], r[q]);
             y[q] = fma(aq, p[q], y[q]);
           }
@@ -473,8 +473,8 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
 #pragma unroll
         for (int q = 0; q < EPT; ++q) {
           u[q] = r[q];
-          if (!col_done(q, dj)) {
-            const double aq = scalar(1, q, alpha);
+          const double aq = scalar(1, q, alpha);
+          if (!col_done(q, dj) && aq != 0.0) {  // 0: as above
             y[q] = fma(aq, p[q], y[q]);
             r[q] = fma(-aq, qv[q], r[q]);
           }
