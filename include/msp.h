@@ -21,11 +21,10 @@
  *     Arguments are validated before any device work is enqueued. msp_last_error()
  *     returns a thread-local message describing the last failure.
  *   - Determinism: identical inputs, seeds and device give bitwise-identical results
- *     (all reductions run in a fixed order; no floating-point atomics). The one exception:
- *     an inner solve runs as one launch whose blocks wait for each other; when other work
- *     keeps them from running together for 50 ms (MSP_INNER_WAIT_MS in the environment sets
- *     another time), the solve is run again with one or two launches per inner step, whose
- *     sums differ by rounding.
+ *     (all reductions run in a fixed order; no floating-point atomics). An inner solve may run
+ *     as one launch whose blocks wait for each other; when other work keeps them from running
+ *     together for 10 ms (MSP_INNER_WAIT_MS in the environment sets another time), one of them
+ *     solves alone, with the same results.
  */
 #ifndef MSP_H
 #define MSP_H

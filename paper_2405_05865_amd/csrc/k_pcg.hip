@@ -25,11 +25,19 @@
 // (pcg_solve clears it before they would wrap).
 //
 // The blocks of a launch have to run together: a launch has at most kPcgMaxBlocks blocks, one
-// per compute unit, so four launches (the hardware queues a process has) fit the chip. A
-// block whose exchange stays incomplete for kPcgWait ticks (other work holds the compute
-// units; MSP_INNER_WAIT_MS in the environment sets another time, a negative one gives up at
-// once) gives up and says so in ctl->fail and the host's mirror; the caller then runs the
-// whole solve on the per-step kernels. So every wait ends.
+// per compute unit, so four launches (the hardware queues a process has) fit the chip. When an
+// exchange stays incomplete for kPcgWait ticks (other work holds the compute units;
+// MSP_INNER_WAIT_MS in the environment sets another time, a negative one does not wait at all)
+// the group's first block solves alone, from the start, with the operands from memory, and the
+// others leave: every wait ends, and the launch always delivers. The rows, the dots and the
+// scalars are formed by the same code in the same order either way, so the results are the
+// same bits whether, and where, a wait ran out (the number of blocks and columns of a group
+// does not enter them either). The next kPcgAlone launches do not try to meet: under lasting
+// contention a solve pays one wait for so many launches.
+//
+// Alone a block reads both operands once per step; per step (whole solves): s = 256, one column:
+// 18 us (4.5 as a group), 16 columns: 23 us (8.0); s = 512, one column: 60 us (4.8), 8 columns:
+// 67 us (7.1); s = 1024, one column: 239 us (5.4).
 //
 // Measured per step, launch and operand loads included: s = 32, direct form, one block: 1.3 us
 // (two kernels per step: 9.9 us); s = 384, recurrence, one column: 3.3 us (6.0 us); s = 512,
@@ -40,6 +48,9 @@
 
 #include "msp_internal.h"
 #include "wave_ops.h"
+
+// every form of a solve (ONE, GROUP, ALONE) rounds alike: the compiler fuses nothing by itself
+#pragma clang fp contract(off)
 
 namespace {
 
@@ -57,9 +68,16 @@ __device__ __forceinline__ void st_word(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A block's view of one solve of KC columns: NM operands (1 or 2 per product), CPL 64-column
-// chunks, RPW rows per wavefront, MULTI: several blocks per group.
-template <int CPL, int RPW, int KC, bool MULTI>
+__device__ __forceinline__ int ld_mark(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// who solves: one block with both operands in its registers, a group of blocks with a share of
+// the rows each, or one block that takes the rows from memory
+enum Form { ONE, GROUP, ALONE };
+
+// A block's view of one solve of KC columns: CPL 64-column chunks, RPW rows per wavefront.
+template <int CPL, int RPW, int KC, Form FORM>
 struct Block {
   static constexpr int SP = CPL * WAVE;              // padded length
   static constexpr int NV = KC * SP;                 // elements of a vector block
@@ -70,7 +88,7 @@ struct Block {
   // partials by 64-element chunk, bc per-column scalars
   struct Shared {
     double xs[NV];
-    double zr[MULTI ? 1 : 2 * NV];
+    double zr[FORM == GROUP ? 1 : 2 * NV];
     double red[3][2][KC * CPL];
     double bc[2][KC];
     int done[KC];
@@ -91,7 +109,7 @@ struct Block {
       }
   }
 
-  // out(jj, row) <- M xs_jj for the wavefront's rows: zr[d] in LDS (one block) or exchange
+  // out(jj, row) <- M xs_jj for the wavefront's rows: zr[d] in LDS or, in a group, exchange
   // words of number `ep` (ex: the buffer of this number, d the product's index)
   static __device__ __forceinline__ void product(const double (&h)[RPW][CPL], int d, int s, int row0, Shared& sh,
                                                  uint64_t* ex, uint32_t ep) {
@@ -116,7 +134,7 @@ struct Block {
       if ((lane & ((1 << SHF) - 1)) == 0) {
         const int row = row0 + i0 + val / KC, jj = val % KC;
         if (row < s) {
-          if constexpr (MULTI) {
+          if constexpr (FORM == GROUP) {
             uint64_t* w = ex + 2 * ((int64_t)(d * KC + jj) * SP + row);
             const uint64_t tag = (uint64_t)ep << 32;
             st_word(w, tag | (uint32_t)__double2loint(mine));
@@ -129,13 +147,22 @@ struct Block {
     }
   }
 
-  // ND product vectors of exchange `ep`, all rows; false when the wait ran out (or another
-  // launch of this solve already gave up)
+  // the same for all rows of M, from memory
+  static __device__ __forceinline__ void product_all(const double* __restrict__ M, int d, int s, Shared& sh) {
+    for (int row0 = threadIdx.x / WAVE * RPW; row0 < s; row0 += NWV * RPW) {
+      double h[RPW][CPL];
+      load_rows(M, s, row0, h);
+      product(h, d, s, row0, sh, nullptr, 0);
+    }
+  }
+
+  // ND product vectors of exchange `ep`, all rows; false when the wait ran out, or did for
+  // another block of the launch
   template <int ND>
-  static __device__ __forceinline__ bool receive(int s, int k0, int k, Shared& sh, const uint64_t* ex, uint32_t ep,
-                                                 int64_t wait, double (&out)[ND][EPT]) {
-    const int tid = threadIdx.x;
-    if constexpr (!MULTI) {
+  static __device__ __forceinline__ bool receive(const PcgArgs& a, Shared& sh, const uint64_t* ex, uint32_t ep,
+                                                 double (&out)[ND][EPT]) {
+    const int tid = threadIdx.x, s = a.s;
+    if constexpr (FORM != GROUP) {
       __syncthreads();
 #pragma unroll
       for (int d = 0; d < ND; ++d)
@@ -148,7 +175,7 @@ struct Block {
     } else {
       uint64_t w[ND][EPT][2];
       int64_t t0 = 0;
-      if (wait < 0) return false;
+      if (a.wait < 0) return false;
       for (int spin = 0;; ++spin) {
         bool ok = true;
 #pragma unroll
@@ -170,10 +197,10 @@ struct Block {
           for (int q = 0; q < EPT; ++q)
             ok = ok && (uint32_t)(w[d][q][0] >> 32) == ep && (uint32_t)(w[d][q][1] >> 32) == ep;
         if (ok) break;
-        if ((spin & 63) == 63) {  // the clock is read once in 64 polls
+        if ((spin & 63) == 63) {  // the clock and the mark are read once in 64 polls
           const int64_t now = (int64_t)wall_clock64();
           if (t0 == 0) t0 = now;
-          else if (now - t0 > wait) return false;
+          else if (now - t0 > a.wait || ld_mark(&a.ctl->alone) > a.serial) return false;
         }
       }
 #pragma unroll
@@ -211,12 +238,12 @@ struct Block {
 
 // MODE 0 (recurrence): z = Minv r and g = G r (G = H Minv) from one exchange, the operator's
 // image of the direction by u_t = g_t + beta_t u_{t-1}. MODE 1 (direct): q = (H + sigma I) p
-// and z = Minv r, an exchange each; nsol chained solves.
-template <int MODE, int CPL, int RPW, int KC, bool MULTI>
-__global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
-  using B = Block<CPL, RPW, KC, MULTI>;
+// and z = Minv r, an exchange each; nsol chained solves. False when a wait ran out.
+template <int MODE, int CPL, int RPW, int KC, Form FORM>
+__device__ __forceinline__ bool solve_block(const PcgArgs& a, typename Block<CPL, RPW, KC, FORM>::Shared& sh) {
+  using B = Block<CPL, RPW, KC, FORM>;
+  constexpr bool MULTI = FORM == GROUP;
   constexpr int EPT = B::EPT, SP = B::SP, NV = B::NV;
-  __shared__ typename B::Shared sh;
   const int tid = threadIdx.x, s = a.s;
   const int grp = blockIdx.x / a.nblk, blk = blockIdx.x % a.nblk;
   const int k0 = a.col0 + grp * KC;
@@ -224,19 +251,6 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
   uint64_t* const exg = a.ex + (int64_t)grp * (MODE == 0 ? 2 : 1) * NV * 2;
   const int64_t exn = (int64_t)a.ex_stride;  // words of one of the two buffers
   uint32_t ep = a.ep0;
-  // the iteration counts of the launch before this one join the total
-  if (blockIdx.x == 0 && tid == 0) {
-    int64_t add = 0;
-    for (int q = 0; q < 2; ++q) add += a.ctl->it[a.parity ^ 1][q];
-    a.ctl->total += add;
-    a.ctl->it[a.parity ^ 1][0] = a.ctl->it[a.parity ^ 1][1] = 0;
-  }
-  if constexpr (MULTI) {  // an earlier launch gave up: its results are discarded anyway
-    if (tid == 0) sh.any = __hip_atomic_load(&a.ctl->fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (sh.any) return;  // uniform in the block
-    __syncthreads();
-  }
   // a thread's elements
   int ecol[EPT];
   int64_t eo[EPT];
@@ -253,7 +267,7 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
   const bool owner = KC == 1 || tid < KC;
   const int oc = KC == 1 ? 0 : min(tid, KC - 1);
   if (tid == 0) sh.stop = 0;
-  double hm[RPW][CPL], mm[RPW][CPL];
+  double hm[RPW][CPL], mm[RPW][CPL];  // (not used alone)
   double r[EPT], y[EPT], p[EPT], u[EPT];
   double v2[2][EPT], v1[1][EPT];
 #pragma unroll
@@ -262,7 +276,7 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
 #pragma unroll
     for (int q = 0; q < EPT; ++q)
       if (ein[q]) y[q] += a.rhs[(int64_t)g * a.k * s + eo[q]];
-  B::load_rows(a.H, s, row0, hm);  // behind the right-hand side: loads return in order
+  if constexpr (FORM != ALONE) B::load_rows(a.H, s, row0, hm);  // behind the right-hand side: loads return in order
 
   auto stage = [&](const double(&x)[EPT]) {
 #pragma unroll
@@ -292,7 +306,15 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
 
   bool failed = false;
   for (int sol = 0; sol < (MODE == 0 ? 1 : a.nsol) && !failed; ++sol) {
-    B::load_rows(a.Minv[sol], s, row0, mm);
+    if constexpr (FORM != ALONE) B::load_rows(a.Minv[sol], s, row0, mm);
+    auto mul_h = [&](int d, uint64_t* ex) {
+      if constexpr (FORM == ALONE) B::product_all(a.H, d, s, sh);
+      else B::product(hm, d, s, row0, sh, ex, ep);
+    };
+    auto mul_m = [&](int d, uint64_t* ex) {
+      if constexpr (FORM == ALONE) B::product_all(a.Minv[sol], d, s, sh);
+      else B::product(mm, d, s, row0, sh, ex, ep);
+    };
     const double sigma = a.sigma[sol];
 #pragma unroll
     for (int q = 0; q < EPT; ++q) {
@@ -328,13 +350,13 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
       bool first = true;
       while (any) {
         uint64_t* ex = exg + (ep & 1) * exn;
-        B::product(mm, 0, s, row0, sh, ex, ep);
-        B::product(hm, 1, s, row0, sh, ex, ep);
+        mul_m(0, ex);
+        mul_h(1, ex);
         if (MULTI && !first && !decide()) {
           ep += 2;  // nobody receives the rows just sent: the next exchange takes their buffer
           break;    // (a slow block may still read the other one)
         }
-        if (!B::template receive<2>(s, k0, a.k, sh, ex, ep, a.wait, v2)) sh.stop = 1;
+        if (!B::template receive<2>(a, sh, ex, ep, v2)) sh.stop = 1;
         ++ep;
         double zg[2][EPT];
 #pragma unroll
@@ -402,12 +424,12 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         // z = Minv r (r is staged), then beta and p
         {
           uint64_t* ex = exg + (ep & 1) * exn;
-          B::product(mm, 0, s, row0, sh, ex, ep);
+          mul_m(0, ex);
           if (MULTI && !first && !decide()) {
             ep += 2;
             break;
           }
-          if (!B::template receive<1>(s, k0, a.k, sh, ex, ep, a.wait, v1)) sh.stop = 1;
+          if (!B::template receive<1>(a, sh, ex, ep, v1)) sh.stop = 1;
           ++ep;
         }
         double z[EPT];
@@ -447,8 +469,8 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
         // q = (H + sigma I) p
         {
           uint64_t* ex = exg + (ep & 1) * exn;
-          B::product(hm, 0, s, row0, sh, ex, ep);
-          if (!B::template receive<1>(s, k0, a.k, sh, ex, ep, a.wait, v1)) sh.stop = 1;
+          mul_h(0, ex);
+          if (!B::template receive<1>(a, sh, ex, ep, v1)) sh.stop = 1;
           ++ep;
         }
         double qv[EPT];
@@ -490,17 +512,44 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
     if (blk == 0 && owner && (KC > 1 || tid == 0)) atomicMax(&a.ctl->it[a.parity][sol], it);
     __syncthreads();  // the next solve reuses the LDS buffers
   }
-  if (failed) {
-    if (tid == 0) {
-      __hip_atomic_store(&a.ctl->fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(a.fail_mirror, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-    return;
-  }
+  if (failed) return false;
   if (blk == 0) {
 #pragma unroll
     for (int q = 0; q < EPT; ++q)
       if (ein[q]) a.out[eo[q]] = y[q];
+  }
+  return true;
+}
+
+template <int MODE, int CPL, int RPW, int KC, bool MULTI>
+__global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
+  constexpr Form FORM = MULTI ? GROUP : ONE;
+  __shared__ typename Block<CPL, RPW, KC, FORM>::Shared sh;
+  const int tid = threadIdx.x;
+  // the iteration counts of the launch before this one join the total
+  if (blockIdx.x == 0 && tid == 0) {
+    int64_t add = 0;
+    for (int q = 0; q < 2; ++q) add += a.ctl->it[a.parity ^ 1][q];
+    a.ctl->total += add;
+    a.ctl->it[a.parity ^ 1][0] = a.ctl->it[a.parity ^ 1][1] = 0;
+  }
+  if constexpr (MULTI) {
+    if (tid == 0) sh.any = ld_mark(&a.ctl->alone) > a.serial;
+    __syncthreads();
+    bool alone = sh.any != 0;  // uniform in the block
+    __syncthreads();
+    if (!alone && !solve_block<MODE, CPL, RPW, KC, FORM>(a, sh)) {
+      if (tid == 0)
+        __hip_atomic_store(&a.ctl->alone, a.serial + kPcgAlone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      alone = true;
+    }
+    if (alone && blockIdx.x % a.nblk == 0) {
+      __shared__ typename Block<CPL, RPW, KC, ALONE>::Shared sa;
+      if (tid == 0) atomicAdd(&a.ctl->nalone, 1);
+      solve_block<MODE, CPL, RPW, KC, ALONE>(a, sa);
+    }
+  } else {
+    solve_block<MODE, CPL, RPW, KC, FORM>(a, sh);
   }
 }
 
@@ -577,6 +626,7 @@ PcgRun pcg_carve(WsCarver& w, int64_t s, int64_t k) {
 hipError_t pcg_reset(hipStream_t st, PcgRun& R) {
   R.next = 1;
   R.parity = 0;
+  R.serial = 0;
   R.wait = kPcgWait;
   if (const char* ms = getenv("MSP_INNER_WAIT_MS")) R.wait = (int64_t)(atof(ms) * 1e5);
   hipError_t e = hipMemsetAsync(R.ctl, 0, sizeof(PcgCtl), st);
@@ -605,6 +655,7 @@ hipError_t pcg_solve(hipStream_t st, PcgRun& R, PcgArgs a, int mode) {
     }
     a.ep0 = (uint32_t)R.next;
     a.parity = R.parity;
+    a.serial = R.serial++;
     a.col0 = g0 * h.kc;
     const int groups = h.groups - g0 < h.per ? h.groups - g0 : h.per;
     const hipError_t e = mode == 0 ? dispatch<0>(st, a, h, groups) : dispatch<1>(st, a, h, groups);

@@ -63,22 +63,14 @@ constexpr int kMaxGammaDraw = 32;
 // MSP_LOG=1 in the environment: one progress line per refinement step, per level-1
 // restart and per quadrature node, on stderr
 bool log_on() {
-  static int on = -1;
-  if (on < 0) {
-    const char* e = getenv("MSP_LOG");
-    on = (e && e[0] && e[0] != '0') ? 1 : 0;
-  }
-  return on == 1;
+  const char* e = getenv("MSP_LOG");
+  return e && e[0] && e[0] != '0';
 }
 constexpr int64_t kMaxS = 2048;    // tall-kernel register layout bound (32 columns per lane)
 constexpr int64_t kMaxK = 1024;
 
 // host mirror slots (pinned, mapped): [level*4 + 0] active count
-enum { SLOT_L1 = 0, SLOT_L2 = 4, SLOT_L3 = 8, SLOT_L3B = 12, SLOT_L0 = 16, SLOT_FAIL = 20 };
-
-// internal status: a one-launch inner solve gave up waiting for its blocks; the solve runs
-// again on the per-step kernels (never returned to the caller)
-constexpr msp_status kPcgGaveUp = (msp_status)15;
+enum { SLOT_L1 = 0, SLOT_L2 = 4, SLOT_L3 = 8, SLOT_L3B = 12, SLOT_L0 = 16 };
 
 // ------------------------------------------------------------------------------------
 // Sketch workspace layout
@@ -530,8 +522,7 @@ struct SolveCtx {
   // general level 3 under level2_form 1 with k <= kL2fMaxK: two kernels per step
   bool use_f = false;
   L2fArgs F{};
-  // inner solves on formed operators in one launch (k_pcg.hip); use_x / use_f (k <= 16) or the
-  // generic step then only run when such a solve gives up
+  // inner solves on formed operators in one launch (k_pcg.hip)
   bool use_p = false;
   PcgRun pcg{};
   int32_t* hf;
@@ -683,7 +674,7 @@ inline volatile int32_t* slot(SolveCtx& c, int i) { return (volatile int32_t*)(c
 
 msp_status sync(SolveCtx& c) {
   MSP_CHECK_HIP(hipStreamSynchronize(c.st));
-  return *slot(c, SLOT_FAIL) ? kPcgGaveUp : MSP_OK;
+  return MSP_OK;
 }
 
 // Waits for the decision that the last deciding kernel of level L publishes to its slot, by
@@ -696,7 +687,6 @@ msp_status wait_decision(SolveCtx& c, const Level& L, int slotid, int* active, i
   uint64_t w = 0;
   for (uint32_t spin = 1;; ++spin) {
     w = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-    if (*slot(c, SLOT_FAIL)) return kPcgGaveUp;
     if (w >> 44 == want) break;
     if (spin % 1024 == 0) {  // an error, or an idle stream without the decision, ends the wait
       const hipError_t e = hipStreamQuery(c.st);
@@ -1169,7 +1159,6 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
     p.parent_done = pdone;
     p.tol = c.o->inner_tol;
     p.max_iter = c.o->max_inner;
-    p.fail_mirror = c.df + SLOT_FAIL;
     MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, 0));
     if (block)
       MSP_CHECK_HIP(launch_gemm_add(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, s, z, n, k, 1.0 / P->lt, r, n,
@@ -1295,7 +1284,6 @@ msp_status gen_solve_m2(SolveCtx& c, const double* r, double* z, const int32_t* 
     p.parent_done = parent_done;
     p.tol = c.o->level3_tol;
     p.max_iter = c.o->max_level3;
-    p.fail_mirror = c.df + SLOT_FAIL;
     MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, 1));
     return MSP_OK;
   }
@@ -1651,7 +1639,7 @@ msp_status choose_segments(SolveCtx& c) {
 }
 
 // the whole solve into X; status from the residuals
-msp_status solve_pass(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B, int64_t ldb, double* X,
+msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B, int64_t ldb, double* X,
                       int64_t ldx, msp_solve_info* info) {
   const msp_solve_opts* o = c.o;
   msp_status st = MSP_OK;
@@ -1692,7 +1680,8 @@ msp_status solve_pass(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const doubl
   PcgCtl ctl{};
   if (c.use_p) MSP_CHECK_HIP(hipMemcpyAsync(&ctl, c.pcg.ctl, sizeof ctl, hipMemcpyDeviceToHost, c.st));
   MSP_CHECK_HIP(hipStreamSynchronize(c.st));
-  if (ctl.fail) return kPcgGaveUp;
+  if (ctl.nalone > 0 && log_on())
+    fprintf(stderr, "[msp] %d inner solves of column groups by one block alone\n", ctl.nalone);
   (c.P->structure == MSP_SYM_PSD ? c.acc.inner_iters : c.acc.level3_iters) +=
       ctl.total + ctl.it[0][0] + ctl.it[0][1] + ctl.it[1][0] + ctl.it[1][1];
   double worst = 0.0;
@@ -1713,24 +1702,6 @@ msp_status solve_pass(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const doubl
   if (st == MSP_ERR_BREAKDOWN) msp_fail(st, "breakdown: p^T A p <= 0");
   if (st == MSP_ERR_NONFINITE) msp_fail(st, "non-finite residual");
   return st;
-}
-
-msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B, int64_t ldb, double* X,
-                      int64_t ldx, msp_solve_info* info) {
-  const msp_status st = solve_pass(c, A_hi, hi_t, B, ldb, X, ldx, info);
-  if (st != kPcgGaveUp) return st;
-  // some other work kept the blocks of an inner solve from running together: the same solve
-  // from the start with one or two launches per inner step
-  if (log_on()) fprintf(stderr, "[msp] an inner solve gave up waiting for its blocks: per-step kernels\n");
-  MSP_CHECK_HIP(hipStreamSynchronize(c.st));
-  c.use_p = false;
-  *slot(c, SLOT_FAIL) = 0;
-  c.acc = msp_solve_info{};
-  c.A_cf = A_hi;
-  c.cf_t = hi_t;
-  c.lam_sw = c.lam;
-  c.evused = 0;
-  return solve_pass(c, A_hi, hi_t, B, ldb, X, ldx, info);
 }
 
 msp_status make_ctx(SolveCtx& c, void* stream, const msp_precond* P, const void* A_hi, msp_dtype hi_t,
@@ -1764,7 +1735,6 @@ msp_status make_ctx(SolveCtx& c, void* stream, const msp_precond* P, const void*
   }
   const int inner_cap = P->structure == MSP_SYM_PSD ? o->max_inner : o->max_level3;
   if (inner_cap > kPcgMaxIter) c.use_p = false;
-  *slot(c, SLOT_FAIL) = 0;
   if (c.use_p) MSP_CHECK_HIP(pcg_reset(c.st, c.pcg));
   // decisions of earlier solves (their streams were synchronised) are numbered 0 from here
   for (int i : {SLOT_L1, SLOT_L2}) *slot(c, i + 2) = *slot(c, i + 3) = 0;

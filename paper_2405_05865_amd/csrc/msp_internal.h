@@ -443,7 +443,8 @@ hipError_t l2f_prec(hipStream_t st, const L2fArgs& a, int t);
 constexpr int kPcgMaxS = 1024;
 constexpr int kPcgMaxBlocks = 64;      // blocks of a launch (they wait for each other)
 constexpr int kPcgMaxIter = 1 << 24;   // exchanges of a launch are numbered in 32 bits
-constexpr int64_t kPcgWait = 5000000;  // 50 ms of the 100 MHz wall clock
+constexpr int64_t kPcgWait = 1000000;  // 10 ms of the 100 MHz wall clock
+constexpr int kPcgAlone = 64;          // launches without a meeting after a wait ran out
 struct PcgShape {
   int cpl;       // 64-column chunks (1, 2, 4, 8, 16); 0: not supported
   int rpw;       // operand rows per wavefront
@@ -456,7 +457,8 @@ struct PcgShape {
 struct PcgCtl {
   int64_t total;   // iterations of the finished solves (largest over the columns, summed)
   int32_t it[2][2];  // [solve parity][chained solve] of the solves not yet in total
-  int32_t fail;    // a wait ran out: the results are not valid
+  int32_t alone;   // launches numbered below this do not try to meet (one block per group solves)
+  int32_t nalone;  // groups whose first block solved alone
 };
 struct PcgRun {  // host side: the buffers and the exchange numbers of one msp_solve
   PcgShape shape;
@@ -465,7 +467,7 @@ struct PcgRun {  // host side: the buffers and the exchange numbers of one msp_s
   size_t words;
   PcgCtl* ctl;
   uint64_t next;
-  int parity;
+  int parity, serial;  // serial: number of the next launch
   int64_t wait;
 };
 struct PcgArgs {
@@ -480,9 +482,8 @@ struct PcgArgs {
   const int32_t* parent_done;
   double tol;
   int max_iter;
-  int32_t* fail_mirror;  // host-mapped copy of ctl->fail
   // set by pcg_solve
-  int s, k, nblk, col0, parity;
+  int s, k, nblk, col0, parity, serial;
   uint64_t* ex;
   int64_t ex_stride;
   PcgCtl* ctl;

@@ -31,7 +31,7 @@
 namespace {
 
 constexpr int kLsGammaMax = 32;  // nonzeros per column the index draw supports
-constexpr int kLsSlot = 32;      // host-mirror slots of the outer iteration (the inner solves use 0..23)
+constexpr int kLsSlot = 32;      // host-mirror slots of the outer iteration (the inner solves use 0..19)
 
 struct LeftSketchWs {
   BucketLists b;
