@@ -1389,7 +1389,7 @@ msp_status gen_core(SolveCtx& c, const double* B, int64_t ldb, double tol, int m
     MSP_CHECK_HIP(fcg_init(c.st, L.S, n, B, ldb, L.r, L.x, nullptr, c.df + SLOT_L1));
   } else {
     MSP_CHECK_HIP(fcg_init(c.st, L.S, m, B, ldb, c.rho, nullptr, nullptr, c.df + SLOT_L1));
-    MSP_CHECK_HIP(launch_axpby(c.st, n, k, 0.0, L.x, n, 0.0, nullptr, 0, L.x, n, nullptr));
+    MSP_CHECK_HIP(hipMemsetAsync(L.x, 0, sizeof(double) * (size_t)(n * k), c.st));
     TRY(sweep_t(c, c.A_sw, c.sw_t, m, n, c.rho, m, L.r, n, nullptr));
   }
   TRY(gen_solve_m1(c, L.r, L.z));
@@ -1495,7 +1495,7 @@ msp_status refine(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const double* B
   const int used0 = c.acc.outer_iters;
   auto left = [&]() { return budget - (c.acc.outer_iters - used0); };
   MSP_CHECK_HIP(launch_coldots(c.st, blen, k, B, ldb, B, ldb, c.bn));
-  MSP_CHECK_HIP(launch_axpby(c.st, n, k, 0.0, c.xh, n, 0.0, nullptr, 0, c.xh, n, nullptr));
+  MSP_CHECK_HIP(hipMemsetAsync(c.xh, 0, sizeof(double) * (size_t)(n * k), c.st));
   MSP_CHECK_HIP(launch_copy_block(c.st, blen, k, B, ldb, c.rh, blen));
   double inner = c.o->refine_inner_tol;
   std::vector<double> prev(k, 1.0), best_rel;
