@@ -314,14 +314,25 @@ hipError_t gemv_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
   return gemv_t<TA, TC, VEC, 4, 8>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
 }
 
+}  // namespace
+
+// Row tiles of the transposed product: enough to fill the chip, in FP64 arithmetic of 32 rows or
+// more (shorter ones cost more in partials than they win: 32 rows x 128 columns took 5 + 10 us
+// as 32 tiles, 3.5 us as one). FP32 sums end with a tile and the tiles are added in FP64, so
+// with FP32 arithmetic the tiles stay as short as 64 of them allow: at 100 and 640 rows the
+// product's error is 3.1e-8 and 5.9e-8, and 9.7e-8 and 1.0e-7 with tiles of 32 rows.
+int gemv_t_row_tiles(int64_t rows, int64_t ctiles, bool fp32) {
+  const int64_t most = std::min<int64_t>(64, fp32 ? rows : rows / 32);
+  return (int)std::max<int64_t>(1, std::min<int64_t>((2048 + ctiles - 1) / ctiles, most));
+}
+
+namespace {
+
 template <class TA, class TC, int VEC>
 hipError_t gemvT_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64_t lda, const double* X,
                    int64_t ldx, double* Y, int64_t ldy, int k, const int32_t* skip, double* part) {
   const int64_t ctiles = (cols + (int64_t)NT * VEC - 1) / ((int64_t)NT * VEC);
-  // enough row tiles to fill the chip, of 32 rows or more (shorter ones cost more in partials
-  // than they win: 32 rows x 128 columns took 5 + 10 us as 32 tiles, 3.5 us as one)
-  int64_t rtiles = (2048 + ctiles - 1) / ctiles;
-  rtiles = std::max<int64_t>(1, std::min<int64_t>(rtiles, std::min<int64_t>(64, rows / 32)));
+  int64_t rtiles = gemv_t_row_tiles(rows, ctiles, sizeof(TC) == 4);
   const int64_t rpt = (rows + rtiles - 1) / rtiles;
   rtiles = (rows + rpt - 1) / rpt;
   const int direct = rtiles == 1;

@@ -185,6 +185,7 @@ hipError_t launch_gemm_t(hipStream_t st, const void* A, msp_dtype a_t, int64_t r
 // Y[:, j] = A^T X[:, j]  (A rows x cols row-major; X length rows; Y length cols)
 // part: scratch of gemv_t_part_doubles(rows, cols, k) doubles
 size_t gemv_t_part_doubles(int64_t rows, int64_t cols, int64_t k);
+int gemv_t_row_tiles(int64_t rows, int64_t ctiles, bool fp32);  // for ctiles column tiles
 hipError_t launch_gemv_t(hipStream_t st, const void* A, msp_dtype a_t, int64_t rows, int64_t cols, int64_t lda,
                          const double* X, int64_t ldx, double* Y, int64_t ldy, int64_t k, const int32_t* skip,
                          double* part);
