@@ -542,8 +542,8 @@ struct SolveCtx {
 // 161 ms, s = 700, k = 2 84 against 91; two launches: s = 520, k = 3 141 against 102); the
 // general level 3 costs 10 to 36 us per step (n = 3000, s = 700: k = 2, one launch, 12.6 against
 // 25.5 ms, k = 4, two, 22.6 against 30.0, k = 8, four, 42.0 against 36.9). Beyond 16 columns a
-// step costs 42 us (s = 512, k = 24, two launches: 156 against 344 ms; s = 375, k = 64, four
-// launches: 71 against 108, k = 128, seven: 121 against 110).
+// step costs 42 us (PSD, n = 3000: s = 512, k = 24, two launches: 28 against 64 ms; s = 375, k =
+// 64, four launches: 60 against 96; s = 700, k = 17, nine: 77 against 58).
 bool pcg_wins(int64_t s, int64_t k, bool psd) {
   const PcgShape h = pcg_shape(s, k);
   return h.cpl > 0 && h.launches <= (k > kL2xMaxK ? 4 : (psd ? 1 : 2));
@@ -602,18 +602,21 @@ size_t solve_layout(WsCarver& w, const msp_precond* P, int64_t k, SolveCtx* c, i
   // which is exact in exact arithmetic but drifts from H p when H and M are as
   // ill-conditioned as the general level-3 matrices (A~^T A~ with kappa(A)^2 spread): there
   // the recurrence iterate stalls near 1e-4 relative error where direct products reach
-  // 1e-7, and the outer levels take about three times the oracle's steps
+  // 1e-7, and the outer levels take about three times the oracle's steps. A PSD matrix can be
+  // that hard too (n = 1000, s = 256, 128 eigenvalues from 1e6 to 1e2 above a floor of 0.1, lam =
+  // 1e-3: no convergence with the recurrence, 11 level-1 steps with direct products), so wider
+  // blocks, whose step is bound by the products and not by the exchange, take direct products
   const bool psd = P->structure == MSP_SYM_PSD;
   const bool use_x = form == 1 && psd && s >= kGemmMinK && s <= kL2xMaxS && k <= kL2xMaxK;
-  // whole inner solves in one launch: the PSD level 2 by the same recurrence, the general
-  // level 3 by direct products
+  // whole inner solves in one launch: the PSD level 2 by the same recurrence for the same
+  // columns, wider blocks and the general level 3 by direct products
   const bool use_p = form == 1 && s >= kGemmMinK && (psd || l3k == 2) && pcg_wins(s, k, psd);
   PcgRun pcg{};
   if (use_p) pcg = pcg_carve(w, s, k);
   L2xArgs X{};
   double* G2 = nullptr;
   if (use_x) X = l2x_carve(w, s, k);
-  if (use_x || (use_p && psd)) G2 = w.take<double>(s * s);
+  if (use_x || (use_p && psd && k <= kL2xMaxK)) G2 = w.take<double>(s * s);
   // the general level 3 as two kernels per step (level2_form 1, at most kL2fMaxK columns)
   const bool use_f = form == 1 && P->structure == MSP_GENERAL && l3k == 2 && k <= kL2fMaxK && s <= kL2fMaxS;
   L2fArgs F{};
@@ -1090,7 +1093,7 @@ msp_status build_explicit(SolveCtx& c) {
     else
       MSP_CHECK_HIP(launch_gram_f32(c.st, (const float*)P->Y, n, s, P->ldy, c.H2, c.gtmp, sp));
     MSP_CHECK_HIP(launch_combine_sym(c.st, s, 1.0, c.H2, P->lt, P->Wm, 0.0, c.H2));
-    if (c.use_x || c.use_p) TRY(form_g(c, c.H2, P->Minv, c.G2));
+    if (c.G2) TRY(form_g(c, c.H2, P->Minv, c.G2));
     return invert_h2(c);
   }
   int nb = 0;
@@ -1148,9 +1151,9 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
         launch_y_z(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, k, 1.0 / P->lt, r, n, -1.0 / P->lt, pdone, z, n));
     return MSP_OK;
   }
-  if (c.use_p) {  // the whole solve in one launch, H applied through G2 = H M2^{-1}
+  if (c.use_p) {  // the whole solve in one launch, H applied through G2 = H M2^{-1} or directly
     PcgArgs p{};
-    p.H = c.G2;
+    p.H = c.G2 ? c.G2 : c.H2;
     p.Minv[0] = P->Minv;
     p.nsol = 1;
     if (block) p.rhs = c.rhs2;
@@ -1159,7 +1162,7 @@ msp_status psd_solve_m1(SolveCtx& c, const double* r, double* z) {
     p.parent_done = pdone;
     p.tol = c.o->inner_tol;
     p.max_iter = c.o->max_inner;
-    MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, 0));
+    MSP_CHECK_HIP(pcg_solve(c.st, c.pcg, p, c.G2 ? 0 : 1));
     if (block)
       MSP_CHECK_HIP(launch_gemm_add(c.st, P->Y, P->y_t, n, s, P->ldy, c.L2.x, s, z, n, k, 1.0 / P->lt, r, n,
                                     -1.0 / P->lt, pdone, c.gemmpart, c.gemmpart_n));
