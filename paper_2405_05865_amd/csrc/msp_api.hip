@@ -478,6 +478,7 @@ struct StepGraphs {
   hipStream_t st = nullptr;   // the solve's stream (synchronised before destruction)
   hipStream_t cap = nullptr;  // capture stream
   std::map<std::tuple<int, const void*, const void*, const void*>, hipGraphExec_t> exec;
+  int64_t replays = 0;
   ~StepGraphs() {
     if (!exec.empty() && st) (void)hipStreamSynchronize(st);
     for (auto& e : exec) (void)hipGraphExecDestroy(e.second);
@@ -874,6 +875,7 @@ msp_status run_l2(SolveCtx& c, const L2Step& a_in, const double* W, int slotid, 
     hipGraphExec_t ex = nullptr;
     TRY(l2_graph(c, a, M, chunk, &ex));
     MSP_CHECK_HIP(hipGraphLaunch(ex, c.st));
+    ++c.graphs.replays;
     issued = chunk;
     TRY(sync(c));
     if (*slot(c, slotid) == 0 || issued >= cap) {
@@ -945,6 +947,7 @@ msp_status run_l2x(SolveCtx& c, const L2xArgs& x, int slotid, int* last, int64_t
     hipGraphExec_t ex = nullptr;
     TRY(step_graph(c, x, chunk, &ex));
     MSP_CHECK_HIP(hipGraphLaunch(ex, c.st));
+    ++c.graphs.replays;
     issued = chunk;
     TRY(sync(c));
     if (*slot(c, slotid) == 0 || issued >= cap) {
@@ -1012,6 +1015,7 @@ msp_status run_l2f(SolveCtx& c, const L2fArgs& f, int slotid, int* last, int64_t
     hipGraphExec_t ex = nullptr;
     TRY(l2f_graph(c, f, chunk, &ex));
     MSP_CHECK_HIP(hipGraphLaunch(ex, c.st));
+    ++c.graphs.replays;
     issued = chunk;
   }
   int want = chunk;
@@ -1685,6 +1689,8 @@ msp_status solve_into(SolveCtx& c, const void* A_hi, msp_dtype hi_t, const doubl
   MSP_CHECK_HIP(hipStreamSynchronize(c.st));
   if (ctl.nalone > 0 && log_on())
     fprintf(stderr, "[msp] %d inner solves of column groups by one block alone\n", ctl.nalone);
+  if (c.graphs.replays > 0 && log_on())
+    fprintf(stderr, "[msp] %zu step graphs, %lld replays\n", c.graphs.exec.size(), (long long)c.graphs.replays);
   (c.P->structure == MSP_SYM_PSD ? c.acc.inner_iters : c.acc.level3_iters) +=
       ctl.total + ctl.it[0][0] + ctl.it[0][1] + ctl.it[1][0] + ctl.it[1][1];
   double worst = 0.0;
