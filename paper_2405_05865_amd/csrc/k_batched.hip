@@ -472,8 +472,10 @@ __device__ __attribute__((noinline)) void yz_chunks(const Job& J, int ch0, int c
   if (ch < ch1) yz_chunk<TY, 1>(J, ch);
 }
 
-// mode 4: out[ch][j][c] = sum over the rows of part ch (batch_yt_rows) of Y[row, c] rhs_j[row];
-// the 16-column tiles of Y are the MFMA rows and the part's rows the reduction
+// mode 4: out[ch][j][c] = sum over the rows of chunk ch of Y[row, c] rhs_j[row]; the 16-column
+// tiles of Y are the MFMA rows and the chunk's rows the reduction. (Parts of four chunks, for
+// fewer partials, are no faster: whole solves with 16 columns, F32, 8 systems of 2000 rows 65
+// against 58 ms, 4 of 10000 626 against 612, 3 of 16000 1153 against 1140.)
 template <class TY>
 __device__ __attribute__((noinline)) void ytr_chunks(const Job& J, int ch0, int ch1) {
   const int w = wave_id(), lane = lane_id(), i = lane & 15, g = lane >> 4;
@@ -482,9 +484,8 @@ __device__ __attribute__((noinline)) void ytr_chunks(const Job& J, int ch0, int 
   const int jb = i < J.k ? i : J.k - 1;
   const TY* Y = (const TY*)J.A;
   const double* V = J.rhs + (int64_t)jb * J.ldr;
-  const int chr = batch_yt_rows(J.n);
   for (int ch = ch0; ch < ch1; ++ch) {
-    const int rb = ch * chr, re = min(J.n, rb + chr);
+    const int rb = ch * CHR, re = min(J.n, rb + CHR);
     for (int tile = w; tile < T; tile += NW) {
       const int c0 = tile * 16;
       const int col = min(c0 + i, s - 1);
@@ -560,18 +561,13 @@ __device__ __forceinline__ bool claim_slice(int32_t* p, int e) {
                                                     __HIP_MEMORY_SCOPE_AGENT);
       });
 }
-// parts of a job: row chunks, mode 4 in its own length
-__device__ __forceinline__ int job_parts(int n, int mode) {
-  const int chr = mode == 4 ? batch_yt_rows(n) : CHR;
-  return (n + chr - 1) / chr;
-}
 __device__ __forceinline__ int slice_begin(int s, int nslice, int nch) { return (int)((int64_t)s * nch / nslice); }
 
 // the leader's sweep: slices for the helpers that joined (published as a new epoch),
 // slice 0 itself, then every other slice done by a helper or, unclaimed, by itself
 template <class TLO, class THI, class TY>
 __device__ void run_job(Ctx& c, const Job& J) {
-  const int nch = job_parts(J.n, J.mode);
+  const int nch = (J.n + CHR - 1) / CHR;
   BatchTeam* T = c.S.team;
   if (threadIdx.x == 0) {
     int H = 0;
@@ -697,14 +693,13 @@ struct Batch {
     run_job<TLO, THI, TY>(c, J);
   }
 
-  // b2 = Y^T r1 from the partials of batch_yt_rows rows (16-column tiles of Y as MFMA rows,
-  // the part's rows as the reduction), added in their order
+  // b2 = Y^T r1 from the chunks' partials, added in their order
   static __device__ void yt_r(Ctx& c) {
     PhaseTimer tm(c, BT_YT);
     const Job J{c.S.Y, c.S.ldy, nullptr, 0, nullptr, c.r1, c.ldn, c.S.ypart, nullptr, 0.0, c.n, c.s, c.ldn, c.k, 4};
     __syncthreads();
     run_job<TLO, THI, TY>(c, J);
-    const int nch = job_parts(c.n, 4);
+    const int nch = (c.n + CHR - 1) / CHR;
     for (int t = threadIdx.x; t < c.k * c.s; t += NTB) {
       const int j = t / c.s, cc = t % c.s;  // element t of every partial
       double v = 0.0;
@@ -1380,7 +1375,7 @@ __device__ void serve(const BatchSys& S, int h, int k, double* part, JobSh* js) 
       const Job J{mode == 0 ? S.A_lo : (yjob ? S.Y : S.A_hi),
                   yjob ? S.ldy : S.lda,
                   js->bv, js->ldb, js->x, js->rhs, js->ldr, js->out, S.cpart, js->lam, S.n, js->ncols, S.ldn, k, mode};
-      const int nch = job_parts(S.n, mode);
+      const int nch = (S.n + CHR - 1) / CHR;
       do_chunks<TLO, THI, TY>(J, slice_begin(h, ns, nch), slice_begin(h + 1, ns, nch), part);
       if (threadIdx.x == 0) st_rel(&T->done[h], js->epoch);  // after the barrier that ended the slice
     }

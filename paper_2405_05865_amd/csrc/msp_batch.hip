@@ -58,9 +58,8 @@ size_t batch_layout(WsCarver& w, int32_t nsys, const msp_system* sys, int kcap, 
     const int64_t n = P->n, s = P->s;
     double* H = w.take<double>(s * s);
     const size_t nch = (size_t)((n + MSP_BATCH_CHR - 1) / MSP_BATCH_CHR);
-    const size_t nyt = (size_t)((n + batch_yt_rows(n) - 1) / batch_yt_rows(n));
     double* cp = w.take<double>(nch * MSP_BATCH_KMAX);
-    double* yp = w.take<double>(nyt * MSP_BATCH_KMAX * s);
+    double* yp = w.take<double>(nch * MSP_BATCH_KMAX * s);
     double* v = w.take<double>((size_t)kcap * (11 * round8(n) + 7 * round8(s)));
     float* f = w.take<float>((size_t)kcap * round8(n));
     if (L) {

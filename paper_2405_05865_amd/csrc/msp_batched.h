@@ -45,14 +45,10 @@ struct BatchSys {
   double lam, lt;     // lambda and lambda~ = lambda + lambda0
   BatchTeam* team;    // cooperation record
   double* cpart;      // per-chunk partials of <x, A x>: [ceil(n / MSP_BATCH_CHR)][MSP_BATCH_KMAX]
-  double* ypart;      // partials of Y^T r: [ceil(n / batch_yt_rows(n))][MSP_BATCH_KMAX][s]
+  double* ypart;      // per-chunk partials of Y^T r: [ceil(n / MSP_BATCH_CHR)][MSP_BATCH_KMAX][s]
   int32_t id;         // position in the caller's array
   int32_t pad;
 };
-
-// Rows per partial of Y^T r: a chunk, and four for long systems, whose leader would otherwise
-// read more partials than it saves.
-inline constexpr int batch_yt_rows(int64_t n) { return n > 8192 ? 4 * MSP_BATCH_CHR : MSP_BATCH_CHR; }
 
 struct BatchPrm {
   double tol, inner_tol, refine_tol;

@@ -1,4 +1,4 @@
-"""Batched systems past the line where Y^T r takes parts of four chunks, with helpers and without."""
+"""Batched systems of more than 8192 rows, with helpers and without: the same bits."""
 import re
 
 import numpy as np
@@ -17,7 +17,7 @@ def _psd(n):
     return ((a + a.T) / 2).contiguous()
 
 
-# one past the line, a last part of one row, and whole parts; beside a short system
+# last chunks of one row and whole chunks; beside a short system
 @pytest.mark.parametrize("n,k", [(8193, 3), (9217, 1), (9216, 16)])
 def test_long_systems(n, k, monkeypatch, capfd):
     print(f"case batched long n={n} k={k}", flush=True)
