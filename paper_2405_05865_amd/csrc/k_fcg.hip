@@ -196,9 +196,8 @@ __global__ void __launch_bounds__(NT) k_alpha_dot(FcgState S, int64_t len, const
 
 __global__ void __launch_bounds__(NT) k_update(FcgState S, int64_t len, double* __restrict__ x,
                                               double* __restrict__ r, double* __restrict__ r_old,
-                                              const double* __restrict__ p, const double* __restrict__ q, double tol,
-                                              int32_t max_iter, int32_t* mirror, const double* __restrict__ pq_part,
-                                              int nparts, int decide) {
+                                              const double* __restrict__ p, const double* __restrict__ q,
+                                              const double* __restrict__ pq_part, int nparts, int decide) {
   __shared__ double sh[NT / WAVE];
   const int j = blockIdx.y;
   const bool live = S.done[j] == 0;
@@ -640,8 +639,8 @@ hipError_t fcg_alpha_dot(hipStream_t st, FcgState S, int64_t len, const double* 
 hipError_t fcg_update(hipStream_t st, FcgState S, int64_t len, double* x, double* r, double* r_old, const double* p,
                       const double* q, double tol, int32_t max_iter, int32_t* mirror, const double* pq_part,
                       int nparts) {
-  hipLaunchKernelGGL(k_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, x, r, r_old, p, q, tol,
-                     max_iter, mirror, pq_part, nparts, 1);
+  hipLaunchKernelGGL(k_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, x, r, r_old, p, q, pq_part,
+                     nparts, 1);
   hipLaunchKernelGGL(k_decide, dim3(1), dim3(NTD), 0, st, S, (int)grid_x(len), tol, max_iter, mirror,
                      pq_part ? BRK_FLAG : BRK_NONE);
   return hipGetLastError();
@@ -663,8 +662,8 @@ hipError_t fcg_step(hipStream_t st, FcgState S, int64_t len, double* x, double* 
 // the same update without the convergence decision (the general path decides on rho)
 hipError_t fcg_update_nodecide(hipStream_t st, FcgState S, int64_t len, double* x, double* r, double* r_old,
                                const double* p, const double* q) {
-  hipLaunchKernelGGL(k_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, x, r, r_old, p, q, 0.0, 0,
-                     nullptr, nullptr, 0, 0);
+  hipLaunchKernelGGL(k_update, dim3(grid_x(len), (unsigned)S.k), dim3(NT), 0, st, S, len, x, r, r_old, p, q, nullptr, 0,
+                     0);
   return hipGetLastError();
 }
 

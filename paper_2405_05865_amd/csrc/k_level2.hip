@@ -751,7 +751,6 @@ const double* l2_groups(const L2Step& a, int* ng) {
   return a.part + (size_t)a.nbC * a.k * a.s;
 }
 
-
 int l2_blocks(int64_t n) {
   int64_t b = (n + 31) / 32;
   if (b > 1024) b = 1024;

@@ -307,7 +307,8 @@ hipError_t gemv_k(hipStream_t st, const TA* A, int64_t rows, int64_t cols, int64
   if (k == 1) return gemv_t<TA, TC, VEC, 4, 1, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
   // rows per block and loads in flight, us per FP64 sweep: two columns, 4 rows x 2 loads 45 (n =
   // 6000) and 6.2 (n = 2048), 8 x 1 63 and 12.5; four columns, 8 x 2 52 and 206 (n = 6000, 12000), 4
-  // x 1 63 and 225, but 10.9 against 7.4 at n = 1024 and 35 against 29 at n = 4096 (too few blocks)
+  // x 1 63 and 225, but 10.9 against 7.4 at n = 1024 and 35 against 29 at n = 4096 (too few blocks;
+  // the line: n = 4900 42.1 against 40.9, 5100 44.5 against 45.4)
   if (k == 2) return gemv_t<TA, TC, VEC, 4, 2, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
   if (k <= 4 && rows >= 5000 && sizeof(TA) == 8) return gemv_t<TA, TC, VEC, 8, 4, 2>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);
   if (k <= 4) return gemv_t<TA, TC, VEC, 4, 4>(st, A, rows, cols, lda, X, ldx, Y, ldy, k, lam, diag, skip, dot_part, nblocks);

@@ -1747,7 +1747,7 @@ msp_status make_ctx(SolveCtx& c, void* stream, const msp_precond* P, const void*
   if (c.use_p) MSP_CHECK_HIP(pcg_reset(c.st, c.pcg));
   // decisions of earlier solves (their streams were synchronised) are numbered 0 from here
   for (int i : {SLOT_L1, SLOT_L2}) *slot(c, i + 2) = *slot(c, i + 3) = 0;
-  for (Level* L : {&c.L0, &c.L1, &c.L2, &c.L3}) MSP_CHECK_HIP(hipMemsetAsync(L->S.counter, 0, sizeof(int32_t), c.st));
+  for (Level* L : {&c.L2, &c.L3}) MSP_CHECK_HIP(hipMemsetAsync(L->S.counter, 0, sizeof(int32_t), c.st));
   MSP_CHECK_HIP(hipMemsetAsync(c.l2b, 0, sizeof(double) * l2_bpart_doubles(c.s, k), c.st));
   return MSP_OK;
 }

@@ -242,7 +242,7 @@ struct FcgState {
   int32_t* done;
   int32_t* iters;
   int32_t* active;   // [1]
-  int32_t* counter;  // [1] last-block ticket (reset by the last block)
+  int32_t* counter;  // [1] last-block ticket of k_level2.hip (reset by the last block)
   double* part;      // per-block partials, >= fcg_part_doubles(len, k)
   int32_t* brk;      // [k] breakdown marker written by block 0 of each column
   int32_t* done_next;   // [k] decision taken inside a multi-block kernel, committed by the next

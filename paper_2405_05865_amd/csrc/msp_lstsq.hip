@@ -191,7 +191,6 @@ extern "C" msp_status msp_lstsq(void* stream, const msp_precond* P, const double
   volatile int32_t* host = P->host_flags + kLsSlot;
   msp_solve_info acc{};
   const double abytes = (double)n * (double)d * (a_t == MSP_F64 ? 8.0 : 4.0);
-  MSP_CHECK_HIP(hipMemsetAsync(w.S.counter, 0, sizeof(int32_t), st));
   // the preconditioner: z = (A~^T A~)^{-1} r by the three-level MSP on A~
   auto prec = [&](const double* r, double* z) -> msp_status {
     msp_solve_info ii{};
