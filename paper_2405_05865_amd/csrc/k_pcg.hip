@@ -158,8 +158,8 @@ struct Block {
 
   // ND product vectors of exchange `ep`, all rows; false when the wait ran out, or did for
   // another block of the launch
-  template <int ND>
-  static __device__ __forceinline__ bool receive(const PcgArgs& a, Shared& sh, const uint64_t* ex, uint32_t ep,
+  template <int ND, class Args>
+  static __device__ __forceinline__ bool receive(Args& a, Shared& sh, const uint64_t* ex, uint32_t ep,
                                                  double (&out)[ND][EPT]) {
     const int tid = threadIdx.x, s = a.s;
     if constexpr (FORM != GROUP) {
@@ -239,8 +239,8 @@ struct Block {
 // MODE 0 (recurrence): z = Minv r and g = G r (G = H Minv) from one exchange, the operator's
 // image of the direction by u_t = g_t + beta_t u_{t-1}. MODE 1 (direct): q = (H + sigma I) p
 // and z = Minv r, an exchange each; nsol chained solves. False when a wait ran out.
-template <int MODE, int CPL, int RPW, int KC, Form FORM>
-__device__ __forceinline__ bool solve_block(const PcgArgs& a, typename Block<CPL, RPW, KC, FORM>::Shared& sh) {
+template <int MODE, int CPL, int RPW, int KC, Form FORM, class Args>
+__device__ __forceinline__ bool solve_block(Args& a, typename Block<CPL, RPW, KC, FORM>::Shared& sh) {
   using B = Block<CPL, RPW, KC, FORM>;
   constexpr bool MULTI = FORM == GROUP;
   constexpr int EPT = B::EPT, SP = B::SP, NV = B::NV;
@@ -524,7 +524,11 @@ __device__ __forceinline__ bool solve_block(const PcgArgs& a, typename Block<CPL
 template <int MODE, int CPL, int RPW, int KC, bool MULTI>
 __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
   constexpr Form FORM = MULTI ? GROUP : ONE;
-  __shared__ typename Block<CPL, RPW, KC, FORM>::Shared sh;
+  __shared__ union {
+    typename Block<CPL, RPW, KC, FORM>::Shared sh;
+    typename Block<CPL, RPW, KC, MULTI ? ALONE : ONE>::Shared alone;
+  } lds;
+  auto& sh = lds.sh;
   const int tid = threadIdx.x;
   // the iteration counts of the launch before this one join the total
   if (blockIdx.x == 0 && tid == 0) {
@@ -544,9 +548,13 @@ __global__ void __launch_bounds__(NT) k_pcg(PcgArgs a) {
       alone = true;
     }
     if (alone && blockIdx.x % a.nblk == 0) {
-      __shared__ typename Block<CPL, RPW, KC, ALONE>::Shared sa;
       if (tid == 0) atomicAdd(&a.ctl->nalone, 1);
-      solve_block<MODE, CPL, RPW, KC, ALONE>(a, sa);
+      // the arguments anew from the kernel's segment: kept in registers over the group's solve
+      // they cost it spills (0.9% of whole solves at n = 10007, s = 320, 16 columns, 265 ms)
+      auto seg = (const __attribute__((address_space(4))) PcgArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(seg));
+      __syncthreads();  // the group's LDS is read no more
+      solve_block<MODE, CPL, RPW, KC, ALONE>(*seg, lds.alone);
     }
   } else {
     solve_block<MODE, CPL, RPW, KC, FORM>(a, sh);
